@@ -21,7 +21,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libikv.so")
 ARCH = "gfx950"
 
-SOURCES = ["ikv_api.hip", "k_memory.hip", "k_score.hip", "k_score_mfma.hip", "k_residual.hip",
+SOURCES = ["ikv_api.hip", "k_memory.hip", "k_score.hip", "k_score_mfma.hip", "k_score_narrow.hip", "k_residual.hip",
            "k_residual_mfma.hip", "k_select.hip", "k_decode.hip", "k_compact.hip", "k_prefill.hip", "ikv_session.cpp"]
 
 FLAGS = [

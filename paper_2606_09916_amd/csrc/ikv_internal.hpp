@@ -34,7 +34,7 @@ __host__ __device__ inline int pad16(int R) { return (R + 15) & ~15; }
 //   msplit [units][pad16(R)][256 bf16]  memory rows pre-split into bf16 hi + lo, the
 //          rows past R zero (MFMA only)
 //   part   per-tile (max, sum exp) of every memory row:
-//            MFMA [tiles of 64 or 128][units][R][2] (room for tiles of 64),
+//            MFMA [tiles of 64, or of 32 (one key pass), or chunks][units][R][2],
 //            VALU [units][R][tiles of 256][2]
 //   lse    [units][R][2]          (max, 1/Z) of every memory row, then (MFMA only)
 //          [units][R]             -(max + log2 Z), the seed of the second pass
@@ -113,9 +113,9 @@ __host__ __device__ inline ScoreSizes score_sizes(const ikv_session &s, int L, i
                                                   bool mfma) {
   ScoreSizes z;
   z.msplit = mfma ? align64f(int64_t(units) * pad16(s.R) * 128) : 0;
-  // MFMA: 64-position partials, or one per 128-entry list tile (at most N / 128 + 8 of
-  // them for chunks of up to 1024 positions)
-  z.part = mfma ? align64f((cdiv(s.N, PART_TILE) + 8) * units * s.R * 2)
+  // MFMA: 64-position partials, or (one key pass) one per 32 list entries, at most N / 32 +
+  // 32 of them for chunks of up to 1024 positions
+  z.part = mfma ? align64f((s.R <= STASH_MAX_R ? cdiv(s.N, 32) + 36 : cdiv(s.N, PART_TILE) + 8) * units * s.R * 2)
                 : align64f(int64_t(units) * s.R * cdiv(s.N, SCORE_TILE) * 2);
   z.lse = align64f(int64_t(units) * s.R * (mfma ? 3 : 2));
   z.lse_pairs = int64_t(units) * s.R * 2;

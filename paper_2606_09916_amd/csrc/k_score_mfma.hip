@@ -25,18 +25,9 @@
 
 #include "ikv_internal.hpp"
 #include "res_setup.hpp"
+#include "score_mfma.hpp"
 
 namespace ikv {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int MD = 128;          // head dimension of this path
-constexpr int KROW = MD + 8;     // LDS row stride in bf16 (272 B): 16-lane column reads hit 64 distinct banks
-constexpr float LOG2E = 1.4426950408889634f;
-
-__device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
 // M' = M * log2(e) / sqrt(D) split into bf16 hi and lo. Per (unit, row), 256 bf16
 // in fragment order [g 0..3][k-step 0..3][hi 8 | lo 8], where (k-step, g) holds
@@ -122,8 +113,6 @@ __global__ void __launch_bounds__(256) k_msplit(const ikv_session *__restrict__ 
   }
 }
 
-__device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
-
 // Sum over the 16 lanes of a row (lanes 16 q .. 16 q + 15), left in every lane of the row,
 // by DPP lane moves instead of LDS permutes: quad_perm [1,0,3,2] and [2,3,0,1] add within
 // each quad, row_half_mirror adds the other quad of the half row, row_mirror the other
@@ -142,26 +131,6 @@ __device__ __forceinline__ float row16_sum(float v) {
 
 constexpr int RING = 4;                          // LDS stages of key rows
 constexpr int STAGE = MFMA_TILE * MD;            // bf16 per stage (32 KB)
-
-// 16 bytes per lane from global memory straight into LDS at lds_base + 16 * lane.
-// Issued from asm so that the compiler does not serialise LDS reads behind every
-// outstanding load; the waits on these loads are placed by hand.
-__device__ __forceinline__ void dma16(const void *g, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-               :
-               : "s"(lds_base), "v"(g)
-               : "memory", "m0");
-}
-// The same with the non-temporal hint, for the key streams: a key row is read once
-// per pass, and kept in L2 it would push out what the workgroups read again (the
-// memory rows, which every workgroup of a head pair or unit reloads). Measured at
-// Qwen3-8B 32k: first pass 443 -> 412 us, second pass 486 -> 435 us.
-__device__ __forceinline__ void dma16_nt(const void *g, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
-               :
-               : "s"(lds_base), "v"(g)
-               : "memory", "m0");
-}
 
 template <bool PASS_B, bool KBAR>
 __global__ void __launch_bounds__(256) k_score_mfma(const uint16_t *__restrict__ kpool, int64_t num_slots, int L,
@@ -399,20 +368,6 @@ __global__ void __launch_bounds__(256) k_score_mfma(const uint16_t *__restrict__
 // domain. The unit-major pass below is used instead whenever Hkv is even.
 constexpr int KSTAGES = 3;
 constexpr int MSTAGE = 64 * 256;                 // bf16 per memory stage: 64 rows x 512 B
-
-// s_waitcnt vmcnt(n) for a wave-uniform n in 0..12
-__device__ __forceinline__ void vm_wait(int n) {
-  switch (n) {
-    case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
-    case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
-    case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
-    case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
-    case 8: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
-    case 10: asm volatile("s_waitcnt vmcnt(10)" ::: "memory"); break;
-    case 12: asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); break;
-    default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
-  }
-}
 
 constexpr int RING_THREADS = 512;
 
@@ -1349,6 +1304,23 @@ k_score_stats(const uint16_t *__restrict__ kpool, int64_t num_slots, int L, int 
   }
 }
 
+// A list tile's (max, sum of exp2) of one row from those of its 32-entry quarters, of which
+// the ones that hold an entry (`left` entries from the tile's start on) were written.
+__device__ __forceinline__ float2 merge_quarters(const float2 (&v)[4], int left) {
+  float2 q[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) q[c] = left > 32 * c ? v[c] : make_float2(-INFINITY, 0.f);
+  float m = -INFINITY;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) m = fmaxf(m, q[c].x);
+  float zs = 0.f;
+  if (m != -INFINITY)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (q[c].x != -INFINITY) zs += q[c].y * ex2(q[c].x - m);
+  return make_float2(m, zs);
+}
+
 // Per (unit, row): combine the per-tile statistics into (max, 1/Z), log2 domain.
 // A workgroup takes 64 consecutive rows; its eight waves split the tiles (lane =
 // row, so each load instruction reads 512 contiguous bytes), fold them online into
@@ -1363,7 +1335,7 @@ __global__ void __launch_bounds__(512) k_lse_mfma(const ikv_session *__restrict_
                                                   const int32_t *__restrict__ slot_maps,
                                                   const int32_t *__restrict__ qpos, int dead, bool pairs, bool kv,
                                                   int nfold, const uint16_t *__restrict__ kpool, int64_t num_slots,
-                                                  const float *__restrict__ blob, float *__restrict__ shared) {
+                                                  const float *__restrict__ blob, float *__restrict__ shared, bool quarters) {
   __shared__ float sm[8][64], sz[8][64];
   const int b = blockIdx.y;
   const int nkv = kv ? RES_KEYS : 0;
@@ -1384,25 +1356,50 @@ __global__ void __launch_bounds__(512) k_lse_mfma(const ikv_session *__restrict_
   const int units = L * Hkv;
   const int64_t rows = int64_t(units) * s.R;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t i = int64_t(bx) * 64 + lane;
-  if (int64_t(bx) * 64 >= rows) return;
+  // 64 rows per workgroup; 16 with quarter partials (four times the bytes), four lanes per row
+  const int rpw = quarters ? 16 : 64, qe = quarters ? lane >> 4 : 0;
+  const int64_t i = int64_t(bx) * rpw + (quarters ? lane & 15 : lane);
+  if (int64_t(bx) * rpw >= rows) return;
   const bool on = i < rows;
   const ScoreSizes z = score_sizes(s, L, units, MD, resid, true);
   float *base = ws + score_offset(sess, b, L, units, MD, resid, true);
   const float *part = base + z.off_part();
-  // partials: one per ptile positions, or pper per ptile-position chunk (list tiles)
+  // partials: one per ptile positions, or pper per ptile-position chunk (list tiles), each
+  // list tile's four quarters apart where the narrow-tile pass left them (one per 32
+  // entries, those past the chunk's count not written)
   const int64_t tiles = pper > 0 ? cdiv(s.N, ptile) * pper : cdiv(s.N, ptile);
+  const int32_t *cc = reinterpret_cast<const int32_t *>(base + z.off_ccount(s.N));
   float m = -INFINITY, zs = 0.f;
   constexpr int LB = 8;                            // tiles in flight per thread
-  if (on)
+  if (on || quarters)                              // quarters: the lanes of a row exchange their quarters
     for (int64_t k0 = w; k0 < tiles; k0 += 8 * LB) {
       float2 pv[LB];
+      if (quarters) {
+        // lane group qe merges tiles q = qe and qe + 4, then the lanes of a row exchange them
+        float2 v[2][4], mt[2];
 #pragma unroll
-      for (int q = 0; q < LB; ++q) {
-        const int64_t k = k0 + 8 * q;
-        pv[q] = *reinterpret_cast<const float2 *>(part + (min(k, tiles - 1) * rows + i) * 2);
-        if (k >= tiles) pv[q] = make_float2(-INFINITY, 0.f);
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            v[h][e] = *reinterpret_cast<const float2 *>(
+                part + ((4 * min(k0 + 8 * (qe + 4 * h), tiles - 1) + e) * rows + min(i, rows - 1)) * 2);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int k = int(min(k0 + 8 * (qe + 4 * h), tiles - 1)), c = k / pper;
+          mt[h] = merge_quarters(v[h], cc[c] - (k - c * pper) * 128);
+        }
+#pragma unroll
+        for (int q = 0; q < LB; ++q)
+          pv[q] = make_float2(__shfl(mt[q >> 2].x, 16 * (q & 3) + (lane & 15), WAVE),
+                              __shfl(mt[q >> 2].y, 16 * (q & 3) + (lane & 15), WAVE));
+      } else {
+#pragma unroll
+        for (int q = 0; q < LB; ++q)
+          pv[q] = *reinterpret_cast<const float2 *>(part + (min(k0 + 8 * q, tiles - 1) * rows + i) * 2);
       }
+#pragma unroll
+      for (int q = 0; q < LB; ++q)
+        if (k0 + 8 * q >= tiles) pv[q] = make_float2(-INFINITY, 0.f);
 #pragma unroll
       for (int q = 0; q < LB; ++q) {
         const float2 p = pv[q];
@@ -1418,7 +1415,7 @@ __global__ void __launch_bounds__(512) k_lse_mfma(const ikv_session *__restrict_
   sm[w][lane] = m;
   sz[w][lane] = zs;
   __syncthreads();
-  if (w == 0 && on) {
+  if (w == 0 && on && qe == 0) {
     float mx = -INFINITY;
     for (int k = 0; k < 8; ++k) mx = fmaxf(mx, sm[k][lane]);
     double Z = 0.0;
@@ -1603,6 +1600,8 @@ hipError_t launch_score_mfma(const ScoreArgs &a, hipStream_t st) {
       k_msplit<<<dim3(MBAR_PARTS, a.B), 256, 0, st>>>(a.sess_dev, a.M, a.ws, a.scores, p.L, p.Hkv, resid);
     }
   const int chunk = stats ? lch : 0;
+  // groups per tile of the narrow-tile passes, 0: the 128-entry passes
+  const int narrow = a.maxR <= 128 ? narrow_tiles(a) : 0;
   if (stats)
     {
       KTimer kt_("k_score_stats", st);
@@ -1614,6 +1613,12 @@ hipError_t launch_score_mfma(const ScoreArgs &a, hipStream_t st) {
       if (large)
         k_score_stats<4><<<grid, 512, 0, st>>>(kp, p.num_slots, p.L, p.Hkv, p.dead_slot, a.sess_dev, a.slot_maps,
                                                a.ws, a.M, a.scores, resid, chunk, small ? 2 : 0);
+    }
+  else if (a.stash && narrow > 0)
+    {
+      // the one key pass: logits to the stash, per-32-entry row statistics, mean key rows
+      const hipError_t e = launch_score_narrow(a, lch, narrow, st);
+      if (e != hipSuccess) return e;
     }
   else if (a.stash)
     {
@@ -1644,7 +1649,7 @@ hipError_t launch_score_mfma(const ScoreArgs &a, hipStream_t st) {
       KTimer kt_("k_lse_mfma", st);
       k_lse_mfma<<<dim3(unsigned(cdiv(int64_t(units) * a.maxR, 64)), a.B), 512, 0, st>>>(
           a.sess_dev, a.ws, p.L, p.Hkv, false, chunk, 0, a.slot_maps, a.qpos, p.dead_slot, true, false, 0, kp,
-          p.num_slots, a.residual, a.ws_shared);
+          p.num_slots, a.residual, a.ws_shared, false);
     }
     float *umass = a.ws_shared;                     // after the sessions' blocks
     {
@@ -1671,14 +1676,15 @@ hipError_t launch_score_mfma(const ScoreArgs &a, hipStream_t st) {
     // with the matrix-core residual head, this launch also folds its first layer (one
     // item of fold_items() per thread) and builds K', V'
     constexpr int FOLD_WGS = int((fold_items<MD>() + 511) / 512);
+    const bool quarters = a.stash && narrow > 0;
     const bool kv = a.mfma_resid;
     const int nfold = kv ? FOLD_WGS : 0;
     const int extra = resid ? (kv ? RES_KEYS : 0) + nfold + 1 : 0;
     KTimer kt_("k_lse_mfma", st);
-    k_lse_mfma<<<dim3(unsigned(cdiv(int64_t(units) * a.maxR, 64) + extra), a.B), 512, 0, st>>>(
+    k_lse_mfma<<<dim3(unsigned(cdiv(int64_t(units) * a.maxR, quarters ? 16 : 64) + extra), a.B), 512, 0, st>>>(
         a.sess_dev, a.ws, p.L, p.Hkv, resid, stats ? chunk : a.stash ? lch : ring ? PART_TILE : MFMA_TILE,
         a.stash ? lch / MFMA_TILE : 0, a.slot_maps, a.qpos, p.dead_slot, a.stats, kv, nfold, kp, p.num_slots,
-        a.residual, a.ws_shared);
+        a.residual, a.ws_shared, quarters);
   }
   if (a.stash)
     {
@@ -1691,6 +1697,11 @@ hipError_t launch_score_mfma(const ScoreArgs &a, hipStream_t st) {
   const bool ws_small = a.minR <= 64, ws_large = a.maxR > 64;
   if (a.stash)
     ;                                                // scored above
+  else if (narrow > 0)
+    {
+      const hipError_t e = launch_score_narrow(a, lch, narrow, st);
+      if (e != hipSuccess) return e;
+    }
   else if (a.maxR <= 128 && resid)
     {
       KTimer kt_("k_score_ws<true>", st);
