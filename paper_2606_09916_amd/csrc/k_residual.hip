@@ -7,6 +7,8 @@
 // All arithmetic is float32. The rule scores arrive in `scores` and are overwritten.
 #include <math.h>
 
+#include <type_traits>
+
 #include "ikv_internal.hpp"
 #include "res_setup.hpp"
 
@@ -167,7 +169,12 @@ __global__ void __launch_bounds__(256) k_res_kv(const ikv_session *__restrict__ 
 
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
-template <int D>
+// A workgroup takes TK candidates; every output's weights stream past them once, WB loads
+// in flight per thread (one at a time, the loop waited out an L2 round trip per weight). 32
+// candidates read the weights least often; few candidates take 8 or 16 each, so that their
+// workgroups reach every CU. D = 64, 2016 candidates: 164 us at 32 without the batched
+// loads, 63 workgroups. A candidate's sums have the same order at every TK.
+template <int D, int TK>
 __global__ void __launch_bounds__(256) k_residual(const ikv_session *__restrict__ sess,
                                                   const int32_t *__restrict__ slot_maps, int dead,
                                                   float *__restrict__ scores, const float *__restrict__ ws,
@@ -175,8 +182,8 @@ __global__ void __launch_bounds__(256) k_residual(const ikv_session *__restrict_
                                                   int L, int Hkv, bool xattn, bool mfma) {
   constexpr int F = 3 * D + 1;
   constexpr int X = F + HC;
-  constexpr int TK = 32;       // candidates per workgroup
   constexpr int KC = 32;       // query keys per LDS chunk
+  constexpr int WB = 16;       // weights in flight per thread
   __shared__ float xT[X][TK];          // [phi ; c] transposed: xT[i][k]
   __shared__ float ql[TK][HC + 4];     // W_Q phi + b_Q
   __shared__ float kvl[2][KC][HC];     // K', V' chunk
@@ -233,32 +240,54 @@ __global__ void __launch_bounds__(256) k_residual(const ikv_session *__restrict_
   }
   __syncthreads();
 
-  // Q = W_Q phi + b_Q : thread -> output o, 16 candidates
+  // acc[k] += sum over i < n of w[i * stride] * xT[i][k0 + k], i in order
+  auto gemv = [&](auto &acc, const float *w, int64_t stride, int n, int k0) __attribute__((always_inline)) {
+    constexpr int NK = sizeof(acc) / sizeof(float);
+    auto add = [&](float wv, int i) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = 0; k < NK; k += 4) {
+        const float4 xv = *reinterpret_cast<const float4 *>(&xT[i][k0 + k]);
+        acc[k] = fmaf(xv.x, wv, acc[k]);
+        acc[k + 1] = fmaf(xv.y, wv, acc[k + 1]);
+        acc[k + 2] = fmaf(xv.z, wv, acc[k + 2]);
+        acc[k + 3] = fmaf(xv.w, wv, acc[k + 3]);
+      }
+    };
+    const int nb = n / WB * WB;
+    float wv[WB];
+#pragma unroll
+    for (int q = 0; q < WB; ++q) wv[q] = w[q * stride];   // n >= 2 WB
+    for (int i = 0; i < nb; i += WB) {
+      float wn[WB];                                // the next batch, before this one is used
+      const int in = min(i + WB, nb - WB);
+#pragma unroll
+      for (int q = 0; q < WB; ++q) wn[q] = w[(in + q) * stride];
+#pragma unroll
+      for (int q = 0; q < WB; ++q) add(wv[q], i + q);
+#pragma unroll
+      for (int q = 0; q < WB; ++q) wv[q] = wn[q];
+    }
+    for (int i = nb; i < n; ++i) add(w[i * stride], i);
+  };
+
+  // Q = W_Q phi + b_Q : thread -> output o, half of the candidates
   {
-    const int o = t & (HC - 1), k0 = (t >> 7) * 16;
-    float acc[16];
+    constexpr int NK = TK / 2;
+    const int o = t & (HC - 1), k0 = (t >> 7) * NK;
+    float acc[NK];
     const float bq = blob[lay.bQ + o];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) acc[k] = bq;
-    for (int i = 0; i < F; ++i) {
-      const float w = wqT[int64_t(i) * HC + o];
+    for (int k = 0; k < NK; ++k) acc[k] = bq;
+    gemv(acc, wqT + o, HC, F, k0);
 #pragma unroll
-      for (int k = 0; k < 16; k += 4) {
-        const float4 xv = *reinterpret_cast<const float4 *>(&xT[i][k0 + k]);
-        acc[k] = fmaf(xv.x, w, acc[k]);
-        acc[k + 1] = fmaf(xv.y, w, acc[k + 1]);
-        acc[k + 2] = fmaf(xv.z, w, acc[k + 2]);
-        acc[k + 3] = fmaf(xv.w, w, acc[k + 3]);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 16; ++k) ql[k0 + k][o] = acc[k];
+    for (int k = 0; k < NK; ++k) ql[k0 + k][o] = acc[k];
   }
   __syncthreads();
 
   // cross-attention: thread -> (candidate k, head hh, half of the head's 32 channels)
   {
-    const int k = t >> 3, hh = (t >> 1) & 3, half = t & 1;
+    const bool mine = t < 8 * TK;                  // the other threads only help to load
+    const int k = mine ? t >> 3 : 0, hh = (t >> 1) & 3, half = t & 1;
     const int c0 = hh * 32 + half * 16;
     float q[16], o[16];
 #pragma unroll
@@ -278,7 +307,7 @@ __global__ void __launch_bounds__(256) k_residual(const ikv_session *__restrict_
         kvl[1][p][c] = p < np ? vp[int64_t(p0 + p) * HC + c] : 0.f;
       }
       __syncthreads();
-      for (int p = 0; p < np; ++p) {
+      for (int p = 0; mine && p < np; ++p) {
         float x = 0.f;
 #pragma unroll
         for (int c = 0; c < 16; ++c) x = fmaf(q[c], kvl[0][p][c0 + c], x);
@@ -294,29 +323,20 @@ __global__ void __launch_bounds__(256) k_residual(const ikv_session *__restrict_
       }
     }
     const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
+    if (mine)
 #pragma unroll
-    for (int c = 0; c < 16; ++c) xT[F + c0 + c][k] = o[c] * inv;
+      for (int c = 0; c < 16; ++c) xT[F + c0 + c][k] = o[c] * inv;
   }
   __syncthreads();
 
-  // hidden layer: thread -> hidden unit o, all 32 candidates
+  // hidden layer: thread -> hidden unit o, every candidate
   {
     const int o = t;
     float acc[TK];
     const float b1 = blob[lay.b1 + o];
 #pragma unroll
     for (int k = 0; k < TK; ++k) acc[k] = b1;
-    for (int i = 0; i < X; ++i) {
-      const float w = w1T[int64_t(i) * HIDDEN + o];
-#pragma unroll
-      for (int k = 0; k < TK; k += 4) {
-        const float4 xv = *reinterpret_cast<const float4 *>(&xT[i][k]);
-        acc[k] = fmaf(xv.x, w, acc[k]);
-        acc[k + 1] = fmaf(xv.y, w, acc[k + 1]);
-        acc[k + 2] = fmaf(xv.z, w, acc[k + 2]);
-        acc[k + 3] = fmaf(xv.w, w, acc[k + 3]);
-      }
-    }
+    gemv(acc, w1T + o, HIDDEN, X, 0);
     const float w2 = blob[lay.w2 + o];
     const int wave = t >> 6;
 #pragma unroll
@@ -374,9 +394,18 @@ static hipError_t launch_residual_t(const ScoreArgs &a, hipStream_t st) {
   if (a.mfma_resid) return launch_residual_mfma(a, st);
   {
     KTimer kt_("k_residual<D>", st);
-    k_residual<D><<<dim3(unsigned(cdiv(a.maxN, 32)), a.B), 256, 0, st>>>(
-        a.sess_dev, a.slot_maps, p.dead_slot, a.scores, a.ws, a.ws_shared, a.residual, p.L, p.Hkv,
-        (a.flags & IKV_NO_XATTN) == 0, a.mfma);
+    auto run = [&](auto tk) {
+      constexpr int TK = decltype(tk)::value;
+      k_residual<D, TK><<<dim3(unsigned(cdiv(a.maxN, TK)), a.B), 256, 0, st>>>(
+          a.sess_dev, a.slot_maps, p.dead_slot, a.scores, a.ws, a.ws_shared, a.residual, p.L, p.Hkv,
+          (a.flags & IKV_NO_XATTN) == 0, a.mfma);
+    };
+    // the fewest candidates that keep within about two rounds of one workgroup per CU
+    int64_t n = 0;
+    for (int b = 0; b < a.B; ++b) n += a.sess_host[b].N > a.sess_host[b].C ? a.sess_host[b].N : 0;
+    if (n <= 512 * 8) run(std::integral_constant<int, 8>{});
+    else if (n <= 512 * 16) run(std::integral_constant<int, 16>{});
+    else run(std::integral_constant<int, 32>{});
   }
   return hipGetLastError();
 }
