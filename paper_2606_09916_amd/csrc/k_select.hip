@@ -442,6 +442,11 @@ __global__ void __launch_bounds__(256) k_select_mark(const ikv_session *__restri
 // Scores concentrate in a narrow range, so the passes bin the keys still in play,
 // [lo, hi], by their offset from lo: 11 bits of the actual spread per pass.
 constexpr int SEL_SMALL = 32768;
+// Up to this many positions one workgroup per session beats the cooperative kernel, whose
+// grid barriers and launch cost the same at any size. Selection and redirect of one
+// session, one workgroup against cooperative: 2048 positions 31 / 51 us, 8192 35 / 52,
+// 16,384 44 / 54, 24,576 67 / 64; eight sessions of 16,384 74 / 80, of 24,576 101 / 98.
+constexpr int SEL_ONE_WG = 16384;
 constexpr int SEL_SU = 32;                 // loads in flight per thread while the keys are read
 
 __device__ __forceinline__ uint32_t block_min(uint32_t v, int *red) {
@@ -949,7 +954,7 @@ hipError_t launch_select(const ikv_session *sess_host, const ikv_session *sess_d
   const int64_t keys_off = sel_chunks_before(sess_host, B) * SEL_PART;
   const int64_t res_off = keys_off + total_positions;
   const int64_t gmax = cdiv(maxN, SC_CHUNK);
-  if (maxN > 0 && maxN <= SC_MAXN && gmax * B <= coop_capacity()) {
+  if (maxN > SEL_ONE_WG && maxN <= SC_MAXN && gmax * B <= coop_capacity()) {
     uint32_t *coop = ws + select_coop_off(sess_host, B, total_positions);
     // the barrier stamps of this call: a random per-process tag in bits 40-63, above it
     // a counter of calls (2^37 calls before it wraps), SC_BARS stamps per call

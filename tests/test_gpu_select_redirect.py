@@ -161,3 +161,15 @@ def test_select_barrier_give_up_is_reported(dev, monkeypatch):
     k_o, n_o, t_o = oracle.select_budget(sc.astype(np.float64), _sets(S, rows[0]))
     assert np.array_equal(keep.astype(bool), k_o) and int(n_keep[0]) == n_o
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n,path", [(16384, "k_select_small"), (16385, "k_select_coop")])
+def test_select_one_workgroup_limit(dev, n, path):
+    """Both sides of the length up to which one workgroup per session selects; heavy ties."""
+    ikv.timing(True)
+    try:
+        test_select_long_sessions_exact(dev, (n, 1025, 1), True)
+        names = [name for name, _ in ikv.timing_read()]
+    finally:
+        ikv.timing(False)
+    assert path in names or (path == "k_select_coop" and "k_select_small" in names)
