@@ -8,11 +8,13 @@
 //   k_compact_list  the kept positions in position order, and their count: a workgroup
 //                   per span of positions counts the kept ones before it and lists its
 //                   own (ballot prefix sums over 1024-position rounds);
-//   k_compact_copy  one workgroup per kept index: the pair angles in float64 (they
+//   k_compact_copy  a workgroup per kept index: the pair angles in float64 (they
 //                   reach 1e5 radians at long distances), cos / sin in LDS, then every
 //                   layer's key rows rotated in float32 and rounded once to the pool's
 //                   type, value rows copied.
 #include <math.h>
+
+#include <algorithm>
 
 #include "ikv_internal.hpp"
 
@@ -78,35 +80,50 @@ __global__ void __launch_bounds__(CL_THREADS) k_compact_list(const ikv_session *
 }
 
 constexpr int CC_THREADS = 256;
-constexpr int CC_PP = 4;                         // channel pairs per thread per step
 
-// four consecutive channels: one 8-byte access (bf16) or one 16-byte access (float32);
-// stores round to the pool's type (nearest even for bf16)
-__device__ __forceinline__ void ld4(const uint16_t *p, float *x) {
-  const uint2 v = *reinterpret_cast<const uint2 *>(p);
-  x[0] = __uint_as_float(v.x << 16);
-  x[1] = __uint_as_float(v.x & 0xffff0000u);
-  x[2] = __uint_as_float(v.y << 16);
-  x[3] = __uint_as_float(v.y & 0xffff0000u);
+// 16 bytes of a row: eight channels (bf16) or four (float32). Every row is read once and
+// with the non-temporal hint; stores round to the pool's type (nearest even for bf16).
+typedef unsigned int cc_u32x4 __attribute__((ext_vector_type(4)));
+template <typename T> constexpr int CC_PP = 16 / int(sizeof(T));   // channel pairs per thread per step
+
+__device__ __forceinline__ cc_u32x4 cc_ld(const void *p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const cc_u32x4 *>(p));
 }
-__device__ __forceinline__ void ld4(const float *p, float *x) {
-  const float4 v = *reinterpret_cast<const float4 *>(p);
-  x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+__device__ __forceinline__ void cc_st(void *p, cc_u32x4 v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<cc_u32x4 *>(p));
 }
-__device__ __forceinline__ void st4(uint16_t *p, const float *y) {
-  *reinterpret_cast<uint2 *>(p) =
-      make_uint2(uint32_t(float_to_bf16_bits(y[0])) | (uint32_t(float_to_bf16_bits(y[1])) << 16),
-                 uint32_t(float_to_bf16_bits(y[2])) | (uint32_t(float_to_bf16_bits(y[3])) << 16));
+__device__ __forceinline__ void cc_unpack(cc_u32x4 v, float (&x)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    x[2 * i] = __uint_as_float(v[i] << 16);
+    x[2 * i + 1] = __uint_as_float(v[i] & 0xffff0000u);
+  }
 }
-__device__ __forceinline__ void st4(float *p, const float *y) {
-  *reinterpret_cast<float4 *>(p) = make_float4(y[0], y[1], y[2], y[3]);
+__device__ __forceinline__ void cc_unpack(cc_u32x4 v, float (&x)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x[i] = __uint_as_float(v[i]);
 }
-__device__ __forceinline__ void cp4(uint16_t *d, const uint16_t *s) {
-  *reinterpret_cast<uint2 *>(d) = *reinterpret_cast<const uint2 *>(s);
+__device__ __forceinline__ cc_u32x4 cc_pack(const float (&y)[8]) {
+  cc_u32x4 v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    v[i] = uint32_t(float_to_bf16_bits(y[2 * i])) | (uint32_t(float_to_bf16_bits(y[2 * i + 1])) << 16);
+  return v;
 }
-__device__ __forceinline__ void cp4(float *d, const float *s) {
-  *reinterpret_cast<float4 *>(d) = *reinterpret_cast<const float4 *>(s);
+__device__ __forceinline__ cc_u32x4 cc_pack(const float (&y)[4]) {
+  cc_u32x4 v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = __float_as_uint(y[i]);
+  return v;
 }
+
+// A workgroup walks kept indices blockIdx.x, + gridDim.x, ... CC_WGS workgroups are two
+// rounds of eight per CU: one per position would send those past the kept count through the
+// chip to find that out. CC_U steps of 16-byte loads are in flight per thread, and the first
+// are issued before the angles, whose float64 pow, cos and sin take about as long as a
+// memory round trip.
+constexpr int CC_WGS = 4096;
+constexpr int CC_U = 3;
 
 template <typename T>
 __global__ void __launch_bounds__(CC_THREADS) k_compact_copy(const ikv_session *__restrict__ sess, T *__restrict__ kp,
@@ -115,40 +132,68 @@ __global__ void __launch_bounds__(CC_THREADS) k_compact_copy(const ikv_session *
                                                              const int32_t *__restrict__ dst,
                                                              const int32_t *__restrict__ pos_list,
                                                              const int32_t *__restrict__ n_keep, double base) {
-  __shared__ float cs[64], sn[64];
+  constexpr int PP = CC_PP<T>;
+  __shared__ __align__(16) float cs[64], sn[64];
   const int b = blockIdx.y;
   const ikv_session s = sess[b];
-  const int tk = blockIdx.x;
-  if (tk >= n_keep[b]) return;
-  const int j = pos_list[s.slot_off + tk];
-  const int64_t src = slot_maps[s.slot_off + j], dslot = dst[s.slot_off + tk];
   const int h = D / 2, t = threadIdx.x;
-  if (t < h) {
-    const double ang = double(tk - j) * pow(base, -2.0 * double(t) / double(D));
-    cs[t] = float(cos(ang));
-    sn[t] = float(sin(ang));
-  }
-  __syncthreads();
+  const int nk = n_keep[b];
   const int64_t row = int64_t(Hkv) * D;          // elements of one slot in one layer
-  const int groups = Hkv * (h / CC_PP);          // pair groups per layer
-  for (int g = t; g < L * groups; g += CC_THREADS) {
-    const int l = g / groups, r = g - l * groups;
-    const int hd = r / (h / CC_PP), q = (r - hd * (h / CC_PP)) * CC_PP;
-    const int64_t o_src = (int64_t(l) * num_slots + src) * row + int64_t(hd) * D;
-    const int64_t o_dst = (int64_t(l) * num_slots + dslot) * row + int64_t(hd) * D;
-    float x1[CC_PP], x2[CC_PP], y1[CC_PP], y2[CC_PP];
-    ld4(kp + o_src + q, x1);
-    ld4(kp + o_src + h + q, x2);
+  const int per = h / PP, groups = Hkv * per;    // pair groups per head and per layer
+  const int steps = L * groups;
+  for (int tk = blockIdx.x; tk < nk; tk += gridDim.x) {
+    const int j = pos_list[s.slot_off + tk];
+    const int64_t src = slot_maps[s.slot_off + j], dslot = dst[s.slot_off + tk];
+    cc_u32x4 k1[CC_U], k2[CC_U], v1[CC_U], v2[CC_U];
+    int64_t od[CC_U];
+    int q[CC_U];
+    // steps past the last are clamped: they read its rows again and store nothing
+    auto load = [&](int g0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int e = 0; e < CC_PP; ++e) {
-      const float c = cs[q + e], sv = sn[q + e];
-      y1[e] = x1[e] * c - x2[e] * sv;
-      y2[e] = x2[e] * c + x1[e] * sv;
+      for (int u = 0; u < CC_U; ++u) {
+        const int g = min(g0 + u * CC_THREADS, steps - 1);
+        const int l = g / groups, r = g - l * groups;
+        const int hd = r / per;
+        q[u] = (r - hd * per) * PP;
+        const int64_t in = int64_t(hd) * D + q[u];
+        const int64_t os = (int64_t(l) * num_slots + src) * row + in;
+        od[u] = (int64_t(l) * num_slots + dslot) * row + in;
+        k1[u] = cc_ld(kp + os);
+        k2[u] = cc_ld(kp + os + h);
+        v1[u] = cc_ld(vp + os);
+        v2[u] = cc_ld(vp + os + h);
+      }
+    };
+    load(t);
+    if (t < h) {
+      const double ang = double(tk - j) * pow(base, -2.0 * double(t) / double(D));
+      cs[t] = float(cos(ang));
+      sn[t] = float(sin(ang));
     }
-    st4(kp + o_dst + q, y1);
-    st4(kp + o_dst + h + q, y2);
-    cp4(vp + o_dst + q, vp + o_src + q);
-    cp4(vp + o_dst + h + q, vp + o_src + h + q);
+    __syncthreads();
+    for (int g0 = t;;) {
+#pragma unroll
+      for (int u = 0; u < CC_U; ++u) {
+        if (g0 + u * CC_THREADS >= steps) continue;
+        float x1[PP], x2[PP], y1[PP], y2[PP];
+        cc_unpack(k1[u], x1);
+        cc_unpack(k2[u], x2);
+#pragma unroll
+        for (int e = 0; e < PP; ++e) {
+          const float c = cs[q[u] + e], sv = sn[q[u] + e];
+          y1[e] = x1[e] * c - x2[e] * sv;
+          y2[e] = x2[e] * c + x1[e] * sv;
+        }
+        cc_st(kp + od[u], cc_pack(y1));
+        cc_st(kp + od[u] + h, cc_pack(y2));
+        cc_st(vp + od[u], v1[u]);
+        cc_st(vp + od[u] + h, v2[u]);
+      }
+      g0 += CC_U * CC_THREADS;
+      if (g0 >= steps) break;
+      load(g0);
+    }
+    __syncthreads();                             // the angles are read: the next index may write its own
   }
 }
 
@@ -163,7 +208,7 @@ hipError_t launch_compact(const ikv_pool &pool, const ikv_session *sess_dev, int
   }
   if (maxN > 0) {
     KTimer kt_("k_compact_copy", st);
-    const dim3 grid(unsigned(maxN), B);
+    const dim3 grid(unsigned(std::min(maxN, CC_WGS)), B);
     if (pool.kv_dtype == IKV_BF16)
       k_compact_copy<uint16_t><<<grid, CC_THREADS, 0, st>>>(
           sess_dev, static_cast<uint16_t *>(pool.k_pool), static_cast<uint16_t *>(pool.v_pool), pool.num_slots, pool.L,
