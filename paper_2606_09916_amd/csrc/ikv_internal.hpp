@@ -161,7 +161,8 @@ inline int stats_chunk(int maxN, int head_pairs) {
 __host__ __device__ inline int64_t bitset_words(int64_t num_slots) { return align64f(cdiv(num_slots, 32)); }
 
 // Decode workspace: per (session, layer, query head, split) the partial (m, l, o[D]),
-// stored as all the o rows ([part][D]) followed by all the (m, l) pairs ([part][2]).
+// stored as all the o rows ([part][D]) followed by all the (m, l) pairs ([part][2]). A
+// session's parts follow those of the sessions before it, split fastest.
 __host__ __device__ inline int64_t decode_part_floats(int D) { return D + 2; }
 
 // ---------------------------------------------------------------- storage
@@ -280,7 +281,15 @@ size_t select_workspace_bytes(const ikv_session *sess, int B, int64_t total_posi
 hipError_t launch_redirect(const ikv_session *sess_dev, int B, int64_t num_slots, int32_t *slot_maps,
                            int32_t dead, const uint8_t *keep, int32_t *freed, int32_t *n_freed,
                            int32_t *live, int32_t *n_live, uint32_t *ws, hipStream_t st);
-hipError_t launch_decode(const ikv_pool &pool, const ikv_session *sess_dev, int B, int splits,
+// How a decode call splits the live lists: `cap` splits of a session at most (the grid), and
+// with several sessions `total` splits shared out by their live counts; `parts` bounds the
+// splits of the call (the workspace).
+struct DecodePlan {
+  int cap, total;
+  int64_t parts;
+};
+DecodePlan decode_plan(const ikv_pool &p, const ikv_session *sess_host, int B);
+hipError_t launch_decode(const ikv_pool &pool, const ikv_session *sess_dev, int B, const DecodePlan &plan,
                          const void *q, const int32_t *live, const int32_t *n_live, void *out,
                          float *ws, hipStream_t st);
 
@@ -312,8 +321,6 @@ hipError_t launch_prefill(const ikv_pool &pool, const ikv_session *sess_dev, int
                           const int32_t *hist, const int32_t *n_hist, double base, float decay, float *M,
                           void *q_out, void *out, float *kq, float *ws, int64_t kq_floats, hipStream_t st);
 
-int64_t decode_units(const ikv_pool &p, int B);
-int decode_splits(int live_bound, int64_t units);
 
 // A word of pinned host memory that kernels set (system scope) to report a fault the
 // host cannot see otherwise (a grid barrier that gave up). Allocated on first use and
