@@ -113,22 +113,6 @@ __global__ void __launch_bounds__(256) k_msplit(const ikv_session *__restrict__ 
   }
 }
 
-// Sum over the 16 lanes of a row (lanes 16 q .. 16 q + 15), left in every lane of the row,
-// by DPP lane moves instead of LDS permutes: quad_perm [1,0,3,2] and [2,3,0,1] add within
-// each quad, row_half_mirror adds the other quad of the half row, row_mirror the other
-// half. Each step adds a commutative pair, so every lane holds the same bits.
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float row16_sum(float v) {
-  v += dpp_mov<0xB1>(v);                            // quad_perm [1,0,3,2]
-  v += dpp_mov<0x4E>(v);                            // quad_perm [2,3,0,1]
-  v += dpp_mov<0x141>(v);                           // row_half_mirror
-  v += dpp_mov<0x140>(v);                           // row_mirror
-  return v;
-}
-
 constexpr int RING = 4;                          // LDS stages of key rows
 constexpr int STAGE = MFMA_TILE * MD;            // bf16 per stage (32 KB)
 
@@ -986,16 +970,21 @@ k_score_ws(const uint16_t *__restrict__ kpool, int64_t num_slots, int L, int Hkv
 // rows of its two units sit in registers for the whole chunk and only keys stream,
 // 32 positions x 2 heads (16 KB) per stage through a 4-stage LDS ring, so two
 // workgroups share a CU. Wave w takes head w >> 1 of the pair and memory rows
-// 32 (w & 1) .. + 31 as two 16-row MFMA blocks; per row it keeps an online (max, sum
-// of exp2) over the chunk's candidates and writes one partial per (chunk, unit, row).
-// Non-candidates enter the accumulators as -inf before the MFMAs, so the epilogue
-// needs no mask. The memory rows are read as float32 and split in registers; the
+// 32 (w & 1) .. + 31 as two 16-row MFMA blocks; per row it keeps an online (reference,
+// sum of exp2) over the chunk's candidates and writes one partial per (chunk, unit, row).
+// The accumulators start at minus the row's reference, which moves only when a logit
+// exceeds it by more than ST_SLACK (any reference near the maximum gives the same sum):
+// nearly every tile then costs a maximum, an exp2 and an add per logit. Against a maximum
+// carried from tile to tile (a rescaled sum and a subtraction per logit): 92,300 positions,
+// 384 units, 64 rows 1515 -> 1442 us, 32,768 positions, 288 units, 128 rows 623 -> 585. The
+// memory rows are read as float32 and split in registers; the
 // workgroups of chunk 0 also store the split rows of their units for the second pass
 // and, with the residual head on, the column sums of their rows (a partial of mbar).
 // For a session at or under its budget the pass only fills the scores with -inf.
 constexpr int ST_TILE = 32;                      // positions per stage
 constexpr int ST_STAGE = ST_TILE * 2 * MD;       // bf16 per stage: 32 positions x 2 heads
 constexpr int ST_CHMAX = 1024;                   // positions per chunk at most
+constexpr float ST_SLACK = 8.f;                  // log2: terms of up to 2^8, sums far below the float32 limit
 
 
 // 16 bytes per lane from sbase + voff (scalar base, 32-bit byte offset per lane)
@@ -1021,7 +1010,10 @@ __device__ __forceinline__ void dma16s(const void *sbase, uint32_t voff, uint32_
 // summed over the waves of a head through a small LDS buffer at the top of the next
 // tile and parked in the tile's bias / key-offset entries, which no later step reads;
 // the chunk's masses leave once, at the end: umass[u][slot_off + j] (row stride
-// ustride), zero off the candidates.
+// ustride), zero off the candidates. The MFMA operands are exchanged, so a lane holds eight
+// rows of one position and adds them itself; with positions in registers and rows across
+// lanes, four DPP steps for each of eight sums took 723 us (32,768 positions, 288 units, 128
+// rows), this form 634.
 template <int NW, bool MASS = false>
 __global__ void __launch_bounds__(128 * NW) __attribute__((amdgpu_waves_per_eu(NW, NW)))
 k_score_stats(const uint16_t *__restrict__ kpool, int64_t num_slots, int L, int Hkv, int dead,
@@ -1033,7 +1025,7 @@ k_score_stats(const uint16_t *__restrict__ kpool, int64_t num_slots, int L, int 
   constexpr int KI = 8 / NW;                     // key loads (1 KB each) per wave per stage
   __shared__ __align__(1024) uint16_t ring[ST_STAGES * ST_STAGE];
   __shared__ uint32_t koff[ST_CHMAX];            // byte offset of each position's key rows in the layer
-  __shared__ __align__(16) float bias[ST_CHMAX];  // 0 for a candidate, -inf otherwise
+  __shared__ __align__(16) float bias[MASS ? ST_CHMAX : 1];   // the mass pass: 0 for a candidate, -inf otherwise
   __shared__ float mred[MASS ? 2 * 2 * NW * ST_TILE : 1];   // per tile parity, head, wave: 32 masses
 
   const int b = blockIdx.y;
@@ -1132,17 +1124,21 @@ k_score_stats(const uint16_t *__restrict__ kpool, int64_t num_slots, int L, int 
     // list entries are candidates; the mass pass walks positions and tests them
     const bool cand = in && (!MASS || (slot != dead && !(j < s.pi || (j >= s.qs && j < s.qe))));
     koff[p] = uint32_t(slot) * slot_bytes;
-    bias[p] = cand ? 0.f : -INFINITY;
+    if (MASS) bias[p] = cand ? 0.f : -INFINITY;
   }
-  // the mass pass: seeds of the lane's two rows (-inf past R, so those rows add nothing)
-  float sd[2] = {0.f, 0.f};
+  // what the accumulators start from: minus the lane's two row references (zero until the
+  // first tile sets them), or in the mass pass the seeds of rows r0 + 16 rb + 4 g + i (-inf
+  // past R, so those rows add nothing)
+  f32x4 seed[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
   if constexpr (MASS) {
     const float *nl2 = base + z.off_nl2();
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      const int row = r0 + 16 * rb + r16;
-      sd[rb] = row < R ? nl2[int64_t(u) * R + row] : -INFINITY;
-    }
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = r0 + 16 * rb + 4 * g + i;
+        seed[rb][i] = row < R ? nl2[int64_t(u) * R + row] : -INFINITY;
+      }
   }
   // every compiler-issued load of the set-up is complete before the first key load
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1167,7 +1163,7 @@ k_score_stats(const uint16_t *__restrict__ kpool, int64_t num_slots, int L, int 
       dma16s(kb0, koff[tt * ST_TILE + 2 * (KI * w + k) + (lane >> 5)] + lconst[k], st + k * 1024);
   };
 
-  float Mr[2] = {-INFINITY, -INFINITY}, Zr[2] = {0.f, 0.f};
+  float Mr[2] = {0.f, 0.f}, Zr[2] = {0.f, 0.f};
   auto compute = [&](int tt) {
     const uint16_t *kl = ring + (tt % ST_STAGES) * ST_STAGE;
     bf16x8 ka[2][4];
@@ -1177,58 +1173,78 @@ k_score_stats(const uint16_t *__restrict__ kpool, int64_t num_slots, int L, int 
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) ka[pb][ks] = *reinterpret_cast<const bf16x8 *>(kr + (((4 * ks + g) ^ r16) * 8));
     }
-    // lane (g, r16) of block (pb, rb) holds row r0 + 16 rb + r16 at positions 16 pb + 4 g + i
+    // lane (g, r16) of block (pb, rb) holds row r0 + 16 rb + r16 at positions 16 pb + 4 g + i;
+    // in the mass pass (operands exchanged) rows r0 + 16 rb + 4 g + i at position 16 pb + r16.
+    // The low halves follow all four high ones: two MFMAs on one accumulator wait for each other.
     f32x4 acc[2][2];
 #pragma unroll
-    for (int pb = 0; pb < 2; ++pb) {
-      const float4 bv = *reinterpret_cast<const float4 *>(bias + tt * ST_TILE + 16 * pb + 4 * g);
-      acc[pb][0] = f32x4{bv.x + sd[0], bv.y + sd[0], bv.z + sd[0], bv.w + sd[0]};
-      acc[pb][1] = f32x4{bv.x + sd[1], bv.y + sd[1], bv.z + sd[1], bv.w + sd[1]};
-    }
+    for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) acc[pb][rb] = seed[rb];
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int pb = 0; pb < 2; ++pb)
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-          acc[pb][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[pb][ks], mh[rb][ks], acc[pb][rb], 0, 0, 0);
-          acc[pb][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[pb][ks], ml[rb][ks], acc[pb][rb], 0, 0, 0);
-        }
-    if constexpr (MASS) {
-      // position 16 pb + 4 g + i: its softmax weights under the wave's 32 rows, summed
-      // over the 16 lanes of the lane group
-      float pm[2][4];
-#pragma unroll
-      for (int pb = 0; pb < 2; ++pb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          pm[pb][i] = row16_sum(ex2(acc[pb][0][i]) + ex2(acc[pb][1][i]));
-        }
-      if (r16 == 0) {
-        float *mr = mred + (((tt & 1) * 2 + hh) * NW + (w % NW)) * ST_TILE;
+      for (int lo = 0; lo < 2; ++lo)
 #pragma unroll
         for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) mr[16 * pb + 4 * g + i] = pm[pb][i];
+          for (int rb = 0; rb < 2; ++rb) {
+            const bf16x8 mv = lo ? ml[rb][ks] : mh[rb][ks];
+            acc[pb][rb] = MASS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(mv, ka[pb][ks], acc[pb][rb], 0, 0, 0)
+                               : __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[pb][ks], mv, acc[pb][rb], 0, 0, 0);
+          }
+    if constexpr (MASS) {
+      // the position's softmax weights under the wave's 32 rows: the lane's eight, then
+      // the four lane groups
+      float pm[2];
+#pragma unroll
+      for (int pb = 0; pb < 2; ++pb) {
+        float v = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v += ex2(acc[pb][0][i]) + ex2(acc[pb][1][i]);
+        v += __shfl_xor(v, 16, WAVE);
+        v += __shfl_xor(v, 32, WAVE);
+        pm[pb] = v;
       }
+      if (lane < ST_TILE)                        // position `lane`; off the candidates no mass
+        mred[(((tt & 1) * 2 + hh) * NW + (w % NW)) * ST_TILE + lane] =
+            bias[tt * ST_TILE + lane] == 0.f ? (lane < 16 ? pm[0] : pm[1]) : 0.f;
       return;
     }
+    if (tt == T - 1 && (npos & (ST_TILE - 1)) != 0) {
+      // entries past the list's end
+      const int left = npos - tt * ST_TILE - 4 * g;
+#pragma unroll
+      for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (16 * pb + i >= left) acc[pb][0][i] = acc[pb][1][i] = -INFINITY;
+    }
+    float mx[2];
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
-      float m = Mr[rb];
+      mx[rb] = acc[0][rb][0];
 #pragma unroll
-      for (int pb = 0; pb < 2; ++pb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) m = fmaxf(m, acc[pb][rb][i]);
-      const float e0 = (m == -INFINITY) ? 0.f : m;   // nothing seen yet: every term below is 0
-      float zs = Zr[rb] * ex2(Mr[rb] - e0);
-#pragma unroll
-      for (int pb = 0; pb < 2; ++pb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) zs += ex2(acc[pb][rb][i] - e0);
-      Zr[rb] = zs;
-      Mr[rb] = m;
+      for (int e = 1; e < 8; ++e) mx[rb] = fmaxf(mx[rb], acc[e >> 2][rb][e & 3]);
     }
+    if (__any(fmaxf(mx[0], mx[1]) > ST_SLACK || Zr[0] == 0.f || Zr[1] == 0.f)) {
+      // move the references up to the largest logits (a row's first logits set its reference)
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        const float d = Zr[rb] != 0.f ? fmaxf(mx[rb], 0.f) : mx[rb] == -INFINITY ? 0.f : mx[rb];
+        Mr[rb] += d;
+        Zr[rb] *= ex2(-d);
+#pragma unroll
+        for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[pb][rb][i] -= d;
+        seed[rb] = f32x4{-Mr[rb], -Mr[rb], -Mr[rb], -Mr[rb]};
+      }
+    }
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) Zr[rb] += ex2(acc[e >> 2][rb][e & 3]);
   };
 
   const bool act = __builtin_amdgcn_readfirstlane(r0) < R;   // a wave past the last row only loads
@@ -1285,10 +1301,12 @@ k_score_stats(const uint16_t *__restrict__ kpool, int64_t num_slots, int L, int 
     }
   }
 
-  // merge the four lane groups of each row and store the chunk's partial
+  // merge the four lane groups of each row and store the chunk's partial (a lane that saw a
+  // candidate has a sum of about 1 or more; one that saw none has no reference)
   const int64_t rows = int64_t(units) * R;
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
+    if (Zr[rb] == 0.f) Mr[rb] = -INFINITY;
 #pragma unroll
     for (int o = 16; o < 64; o <<= 1) {
       const float m2 = __shfl_xor(Mr[rb], o, WAVE), z2 = __shfl_xor(Zr[rb], o, WAVE);
