@@ -156,6 +156,10 @@ __global__ void __launch_bounds__(PD) k_prefill_memory(const ikv_session *__rest
 constexpr int PA_WAVES = 8;
 constexpr int PA_THREADS = PA_WAVES * WAVE;
 constexpr int PA_TILE = 64;
+// How far (log2) a logit may rise above its row's reference before the reference moves: the
+// weights stay below 2^8, and nearly every tile needs no exchange between lanes and no
+// rescaling.
+constexpr float PA_SLACK = 8.f;
 constexpr int PA_KROW = PD + 8;
 constexpr int PA_VROW = PA_TILE + 8;
 constexpr int PA_ROWS = 256;                     // query rows of a (layer, KV head) at most: n G <= 256
@@ -205,7 +209,9 @@ __global__ void __launch_bounds__(PA_THREADS) k_prefill_attn(const ikv_session *
   const bool wave_on = 32 * w < nrows;
   const float scale = 1.4426950408889634f / sqrtf(float(PD));
 
-  float m_run[PA_RB], l_run[PA_RB];              // per row block: this lane's row (rows are the lane index c)
+  // Per row block, of this lane's row (rows are the lane index c): the reference of its
+  // weights, and the sum of this lane's own (the four lane groups are added at the end).
+  float m_run[PA_RB], l_run[PA_RB];
   f32x4 o[PA_RB][8];                              // O^T blocks: channel 16 db + 4 g + i, row c
 #pragma unroll
   for (int rb = 0; rb < PA_RB; ++rb) {
@@ -287,12 +293,13 @@ __global__ void __launch_bounds__(PA_THREADS) k_prefill_attn(const ikv_session *
       bf16x8 ph[PA_RB][2], pl[PA_RB][2];
 #pragma unroll
       for (int rb = 0; rb < PA_RB; ++rb) {
-        float tmax = -INFINITY;
+        float tmax = -INFINITY;                     // of this lane's 16 logits, log2 domain
         if (hist_tile) {                            // every key of the tile is history: nothing masked,
 #pragma unroll                                      // the maximum taken on the raw logits
           for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
             for (int i = 0; i < 4; ++i) tmax = fmaxf(tmax, sacc[rb][kb][i]);
+          tmax *= scale;                            // scale > 0: the same value as the maximum of the scaled logits
         } else {
 #pragma unroll
           for (int kb = 0; kb < 4; ++kb)
@@ -305,12 +312,23 @@ __global__ void __launch_bounds__(PA_THREADS) k_prefill_attn(const ikv_session *
               tmax = fmaxf(tmax, x);
             }
         }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 16, WAVE));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, WAVE));
-        if (hist_tile) tmax *= scale;               // scale > 0: the same value as the maximum of the scaled logits
-        const float m_new = fmaxf(m_run[rb], tmax);
-        // a row with no key yet (m_new = -inf) keeps zero weights and sums
-        const float corr = m_run[rb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[rb] - m_new);
+        // a new reference only where a logit is more than PA_SLACK above it, or there is none yet
+        if (!hist_tile || __builtin_amdgcn_ballot_w64(!(tmax - m_run[rb] <= PA_SLACK)) != 0) {
+          tmax = fmaxf(tmax, __shfl_xor(tmax, 16, WAVE));
+          tmax = fmaxf(tmax, __shfl_xor(tmax, 32, WAVE));
+          const float m_new = fmaxf(m_run[rb], tmax);
+          // a row with no key yet (m_new = -inf) keeps zero weights and sums
+          const float corr = m_run[rb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[rb] - m_new);
+          l_run[rb] *= corr;
+          // the outputs are rescaled only when some row's maximum moved (corr = 1 otherwise)
+          if (__builtin_amdgcn_ballot_w64(m_new != m_run[rb]) != 0)
+#pragma unroll
+            for (int db = 0; db < 8; ++db)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) o[rb][db][i] *= corr;
+          m_run[rb] = m_new;
+        }
+        const float m = m_run[rb];
         float psum = 0.f;
         float p[4][4];
         if (hist_tile) {
@@ -318,7 +336,7 @@ __global__ void __launch_bounds__(PA_THREADS) k_prefill_attn(const ikv_session *
           for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              p[kb][i] = __builtin_amdgcn_exp2f(fmaf(sacc[rb][kb][i], scale, -m_new));
+              p[kb][i] = __builtin_amdgcn_exp2f(fmaf(sacc[rb][kb][i], scale, -m));
               psum += p[kb][i];
             }
         } else {
@@ -326,20 +344,11 @@ __global__ void __launch_bounds__(PA_THREADS) k_prefill_attn(const ikv_session *
           for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              p[kb][i] = sacc[rb][kb][i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sacc[rb][kb][i] - m_new);
+              p[kb][i] = sacc[rb][kb][i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sacc[rb][kb][i] - m);
               psum += p[kb][i];
             }
         }
-        psum += __shfl_xor(psum, 16, WAVE);
-        psum += __shfl_xor(psum, 32, WAVE);
-        l_run[rb] = l_run[rb] * corr + psum;
-        // the outputs are rescaled only when some row's maximum moved (corr = 1 otherwise)
-        if (__builtin_amdgcn_ballot_w64(m_new != m_run[rb]) != 0)
-#pragma unroll
-          for (int db = 0; db < 8; ++db)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[rb][db][i] *= corr;
-        m_run[rb] = m_new;
+        l_run[rb] += psum;
         // k index 8 g + e of 32-key step st2 stands for key perm32(g, e)
 #pragma unroll
         for (int st2 = 0; st2 < 2; ++st2)
@@ -404,6 +413,8 @@ __global__ void __launch_bounds__(PA_THREADS) k_prefill_attn(const ikv_session *
   if (!wave_on) return;
 #pragma unroll
   for (int rb = 0; rb < PA_RB; ++rb) {
+    l_run[rb] += __shfl_xor(l_run[rb], 16, WAVE);
+    l_run[rb] += __shfl_xor(l_run[rb], 32, WAVE);
     const int r = 32 * w + 16 * rb + c;
     if (r >= nrows) continue;
     if constexpr (PART) {
