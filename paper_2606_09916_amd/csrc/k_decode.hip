@@ -44,12 +44,12 @@ static int64_t live_bound(const ikv_session &s) {
 // (8192 live, 72 units) that is 7 splits of 1171 positions: the head-group kernel 196 us
 // against 212 with 32 splits of 256 (without the stores, 32 splits ran in 191).
 //
-// Several sessions: a session's splits follow its own live count, so that workgroups of
-// short and long sessions take about the same time, out of `total` splits for all of them.
-// Those fill one round where that gives splits of up to 1.5 k positions, else up to eight
-// rounds of about 1 k positions. With one split per session, 16 sessions of 1158 to 8192
-// live positions (48 layers, 4 KV heads, 768 workgroups) waited on the longest for a third
-// of the time.
+// Several sessions: a session's splits follow its own live count, out of `total` splits for
+// all of them: one round's where those come out even (no split more than 1.4 times the mean;
+// eight sessions of 4160, 48 layers of 4 KV heads, one split each: 535 us, 588 in three
+// rounds), else up to eight rounds of splits of about 1 k positions. With one split per
+// session, 16 sessions of 1158 to 8192 live positions (768 workgroups) waited on the longest:
+// 1754 us, 1511 in eight rounds.
 constexpr int DEC_ROUND = 512;                     // workgroups of one resident round
 constexpr int DEC_MAX_SPLITS = 64;                 // of one session
 constexpr int DEC_SPLIT_POS = 1024;                // positions per split of a call of several rounds
@@ -74,8 +74,17 @@ DecodePlan decode_plan(const ikv_pool &p, const ikv_session *sess_host, int B) {
     return d;
   }
   const int64_t even = sum * units / DEC_ROUND;    // positions per split of a single round
+  const int64_t one = DEC_ROUND / units;           // splits of a single round
+  int64_t need = 0, widest = 0;
+  for (int b = 0; b < B; ++b) {
+    const int64_t n = live_bound(sess_host[b]), k = std::max<int64_t>(1, n * one / sum);
+    need += k;
+    widest = std::max(widest, cdiv(n, k));
+  }
+  const bool fits = need <= one && 5 * widest <= 7 * even;
   const int64_t rounds =
-      std::max<int64_t>(1, std::min<int64_t>(DEC_MAX_ROUNDS, (even + DEC_SPLIT_POS / 2) / DEC_SPLIT_POS));
+      fits ? 1
+           : std::max<int64_t>(1, std::min<int64_t>(DEC_MAX_ROUNDS, (even + DEC_SPLIT_POS / 2) / DEC_SPLIT_POS));
   d.total = int(std::max<int64_t>(1, DEC_ROUND * rounds / units));
   d.cap = clamp(cdiv(longest * d.total, sum) + 1);
   d.parts = std::min<int64_t>(int64_t(B) * d.cap, int64_t(d.total) + B);
