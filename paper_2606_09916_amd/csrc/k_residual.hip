@@ -16,60 +16,9 @@ namespace ikv {
 
 int64_t residual_floats(int D) { return ResLayout(D).total; }
 
-// W_Q^T [F][HC] and W_1^T [F+HC][HIDDEN] so that consecutive threads read consecutive
-// outputs, and the cross-attention columns of W_1 as bf16 hi [HIDDEN][HC] then lo,
-// each 32-wide head block in the MFMA k order of perm32.
-__global__ void k_res_transpose(const float *__restrict__ blob, float *__restrict__ shared, int D) {
-  const ResLayout lay(D);
-  const int64_t F = 3 * D + 1;
-  const int64_t nq = F * HC, n1 = (F + HC) * HIDDEN, nc = int64_t(HIDDEN) * HC;
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  float *wqT = shared;
-  float *w1T = shared + align64f(F * HC);
-  uint16_t *w1c = reinterpret_cast<uint16_t *>(w1T + align64f((F + HC) * HIDDEN));
-  if (i < nq) {
-    const int64_t in = i / HC, o = i - in * HC;
-    wqT[i] = blob[lay.WQ + o * F + in];
-  } else if (i < nq + n1) {
-    const int64_t k = i - nq;
-    const int64_t in = k / HIDDEN, o = k - in * HIDDEN;
-    w1T[k] = blob[lay.W1 + o * (F + HC) + in];
-  } else if (i < nq + n1 + nc) {
-    const int64_t k = i - nq - n1;
-    const int64_t o = k / HC, c = k - o * HC;
-    const float v = blob[lay.W1 + o * (F + HC) + F + c];
-    const uint16_t hi = float_to_bf16_bits(v);
-    const int64_t at = o * HC + (c & ~int64_t(31)) + perm32_inv(int(c & 31));
-    w1c[at] = hi;
-    w1c[nc + at] = float_to_bf16_bits(v - bf16_bits_to_float(hi));
-  }
-}
-
-// Partial column sums of the memory rows: part p sums rows [p*rows/P, (p+1)*rows/P).
-template <int D>
-__global__ void __launch_bounds__(256) k_mbar_part(const ikv_session *__restrict__ sess, const float *__restrict__ M,
-                                                   float *__restrict__ ws, int L, int Hkv, bool mfma) {
-  const int b = blockIdx.y;
-  const ikv_session s = sess[b];
-  if (s.N <= s.C) return;
-  const int units = L * Hkv;
-  const int64_t rows = int64_t(units) * s.R;
-  const int p = blockIdx.x;
-  const int64_t r0 = rows * p / MBAR_PARTS, r1 = rows * (p + 1) / MBAR_PARTS;
-  __shared__ float red[256 / D][D];
-  const int d = threadIdx.x % D, g = threadIdx.x / D;
-  constexpr int NG = 256 / D;
-  float a = 0.f;
-  for (int64_t r = r0 + g; r < r1; r += NG) a += M[s.mem_off + r * D + d];
-  red[g][d] = a;
-  __syncthreads();
-  if (g == 0) {
-    float t = 0.f;
-    for (int k = 0; k < NG; ++k) t += red[k][d];
-    const ScoreSizes z = score_sizes(s, L, units, D, true, mfma);
-    float *misc = ws + score_offset(sess, b, L, units, D, true, mfma) + z.off_misc();
-    misc[int64_t(p) * D + d] = t;
-  }
+__global__ void __launch_bounds__(256) k_res_transpose(const float *__restrict__ blob, float *__restrict__ shared,
+                                                       int D) {
+  res_transpose_item(int64_t(blockIdx.x) * 256 + threadIdx.x, blob, shared, D);
 }
 
 // Per session: mbar and the live query positions (res_setup_body), one workgroup each.
@@ -359,18 +308,13 @@ hipError_t launch_residual_mfma(const ScoreArgs &a, hipStream_t st);
 template <int D>
 static hipError_t launch_residual_t(const ScoreArgs &a, hipStream_t st) {
   const ikv_pool &p = a.pool;
-  const int64_t F = 3 * D + 1;
-  const int64_t n = F * HC + (F + HC) * HIDDEN + int64_t(HIDDEN) * HC;
-  if (!a.mfma_resid)
+  // on the vector-unit path k_score_rest has transposed the weights and left the partial sums
+  // of mbar (on the matrix-core path k_msplit or the first pass leaves those)
+  if (!a.mfma_resid && a.mfma)
     {
       KTimer kt_("k_res_transpose", st);
-      k_res_transpose<<<unsigned(cdiv(n, 256)), 256, 0, st>>>(a.residual, a.ws_shared, D);
+      k_res_transpose<<<unsigned(cdiv(res_transpose_items(D), 256)), 256, 0, st>>>(a.residual, a.ws_shared, D);
     }
-  if (!a.mfma)   // on the matrix-core path k_msplit leaves the partial sums of mbar
-  {
-    KTimer kt_("k_mbar_part<D>", st);
-    k_mbar_part<D><<<dim3(MBAR_PARTS, a.B), 256, 0, st>>>(a.sess_dev, a.M, a.ws, p.L, p.Hkv, a.mfma);
-  }
   if (!a.mfma)   // on the matrix-core path the row-statistics launch did the set-up
     {
       KTimer kt_("k_res_setup<D>", st);

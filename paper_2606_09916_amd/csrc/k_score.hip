@@ -13,6 +13,7 @@
 #include <math.h>
 
 #include "ikv_internal.hpp"
+#include "res_setup.hpp"
 
 namespace ikv {
 
@@ -221,13 +222,12 @@ __global__ void __launch_bounds__(TPB) k_score_rule(const T *__restrict__ kpool,
 }
 
 // ------------------------------------------------------------------ finish
-__global__ void __launch_bounds__(256) k_score_finish(const ikv_session *__restrict__ sess,
-                                                      const int32_t *__restrict__ slot_maps, int dead,
-                                                      float *__restrict__ scores, const float *__restrict__ ws,
-                                                      int L, int units, int D, bool resid) {
-  const int b = blockIdx.y;
+__device__ __forceinline__ void score_finish_wg(int bx, int b, const ikv_session *__restrict__ sess,
+                                                const int32_t *__restrict__ slot_maps, int dead,
+                                                float *__restrict__ scores, const float *__restrict__ ws, int L,
+                                                int units, int D, bool resid) {
   const ikv_session s = sess[b];
-  const int j = blockIdx.x * 256 + threadIdx.x;
+  const int j = bx * 256 + threadIdx.x;
   if (j >= s.N) return;
   float *out = scores + s.slot_off;
   if (s.N <= s.C) {
@@ -247,18 +247,24 @@ __global__ void __launch_bounds__(256) k_score_finish(const ikv_session *__restr
   out[j] = float(acc);
 }
 
+__global__ void __launch_bounds__(256) k_score_finish(const ikv_session *__restrict__ sess,
+                                                      const int32_t *__restrict__ slot_maps, int dead,
+                                                      float *__restrict__ scores, const float *__restrict__ ws, int L,
+                                                      int units, int D, bool resid) {
+  score_finish_wg(int(blockIdx.x), int(blockIdx.y), sess, slot_maps, dead, scores, ws, L, units, D, resid);
+}
+
 // ------------------------------------------------------------------ mean key rows (Eq. 5)
 template <typename T, int D>
-__global__ void __launch_bounds__(256) k_kbar(const T *__restrict__ kpool, int64_t num_slots, int L, int Hkv,
-                                              int dead, const ikv_session *__restrict__ sess,
-                                              const int32_t *__restrict__ slot_maps, float *__restrict__ ws) {
+__device__ __forceinline__ void kbar_wg(int bx, int b, const T *__restrict__ kpool, int64_t num_slots, int L, int Hkv,
+                                        int dead, const ikv_session *__restrict__ sess,
+                                        const int32_t *__restrict__ slot_maps, float *__restrict__ ws) {
   constexpr int TPT = D / 2;          // threads per position, two channels each
   constexpr int TOK = 256 / TPT;
-  const int b = blockIdx.y;
   const ikv_session s = sess[b];
   if (s.N <= s.C) return;
   const int t = threadIdx.x;
-  const int j = blockIdx.x * TOK + t / TPT;
+  const int j = bx * TOK + t / TPT;
   if (j >= s.N) return;
   const int d = (t % TPT) * 2;
   const int units = L * Hkv;
@@ -279,6 +285,38 @@ __global__ void __launch_bounds__(256) k_kbar(const T *__restrict__ kpool, int64
   const float inv = 1.0f / float(units);
   kbar[int64_t(j) * D + d] = a0 * inv;
   kbar[int64_t(j) * D + d + 1] = a1 * inv;
+}
+
+// What is left of a call with the residual head after the second pass and before the head's
+// set-up, in one launch of workgroups that need nothing of each other: block x takes 256
+// positions of the finish, then TOK of the mean key rows, then a part of mbar's sums, then (in
+// the first row of the grid) 256 of the transposed weights. As four launches a small
+// float32 step (one layer, 2048 positions) took 131.6 us, 125.2 as one.
+template <typename T, int D>
+__global__ void __launch_bounds__(256) k_score_rest(const T *__restrict__ kpool, int64_t num_slots, int L, int Hkv,
+                                                    int dead, const ikv_session *__restrict__ sess,
+                                                    const int32_t *__restrict__ slot_maps, const float *__restrict__ M,
+                                                    const float *__restrict__ blob, float *__restrict__ scores,
+                                                    float *__restrict__ ws, float *__restrict__ shared, int nfin,
+                                                    int nkbar) {
+  int x = int(blockIdx.x);
+  const int b = int(blockIdx.y);
+  if (x < nfin) {
+    score_finish_wg(x, b, sess, slot_maps, dead, scores, ws, L, L * Hkv, D, true);
+    return;
+  }
+  x -= nfin;
+  if (x < nkbar) {
+    kbar_wg<T, D>(x, b, kpool, num_slots, L, Hkv, dead, sess, slot_maps, ws);
+    return;
+  }
+  x -= nkbar;
+  if (x < MBAR_PARTS) {
+    mbar_part_wg<D>(b, x, sess, M, ws, L, Hkv);
+    return;
+  }
+  x -= MBAR_PARTS;
+  if (b == 0) res_transpose_item(int64_t(x) * 256 + threadIdx.x, blob, shared, D);
 }
 
 hipError_t launch_residual(const ScoreArgs &a, hipStream_t st);
@@ -309,20 +347,22 @@ static hipError_t launch_score_t(const ScoreArgs &a, hipStream_t st) {
       k_score_rule<T, D, 256><<<dim3(tiles, p.L, a.B), 256, 0, st>>>(kp, p.num_slots, p.L, p.Hkv, p.dead_slot, a.sess_dev,
                                                                      a.slot_maps, a.M, a.ws, resid);
   }
-  {
+  const int nfin = int(cdiv(a.maxN, 256));
+  if (!resid) {
     KTimer kt_("k_score_finish", st);
-    k_score_finish<<<dim3(unsigned(cdiv(a.maxN, 256)), a.B), 256, 0, st>>>(a.sess_dev, a.slot_maps, p.dead_slot,
-                                                                          a.scores, a.ws, p.L, units, D, resid);
+    k_score_finish<<<dim3(unsigned(nfin), a.B), 256, 0, st>>>(a.sess_dev, a.slot_maps, p.dead_slot, a.scores, a.ws, p.L,
+                                                              units, D, resid);
+    return hipGetLastError();
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !resid) return e;
-  constexpr int TOK = 256 / (D / 2);
   {
-    KTimer kt_("k_kbar<T, D>", st);
-    k_kbar<T, D><<<dim3(unsigned(cdiv(a.maxN, TOK)), a.B), 256, 0, st>>>(kp, p.num_slots, p.L, p.Hkv, p.dead_slot,
-                                                                         a.sess_dev, a.slot_maps, a.ws);
+    constexpr int TOK = 256 / (D / 2);
+    const int nkbar = int(cdiv(a.maxN, TOK)), ntr = int(cdiv(res_transpose_items(D), 256));
+    KTimer kt_("k_score_rest<T, D>", st);
+    k_score_rest<T, D><<<dim3(unsigned(nfin + nkbar + MBAR_PARTS + ntr), a.B), 256, 0, st>>>(
+        kp, p.num_slots, p.L, p.Hkv, p.dead_slot, a.sess_dev, a.slot_maps, a.M, a.residual, a.scores, a.ws, a.ws_shared,
+        nfin, nkbar);
   }
-  e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_residual(a, st);
 }

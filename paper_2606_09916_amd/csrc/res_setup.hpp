@@ -340,4 +340,65 @@ __device__ __forceinline__ void res_kv_keys_wg(int key, const ikv_session *__res
   res_kv_frag_store(kf, kf + KVF_BF16 / 2, key, o, a);
 }
 
+// Items of res_transpose_item.
+__host__ __device__ inline int64_t res_transpose_items(int D) {
+  const int64_t F = 3 * D + 1;
+  return F * HC + (F + HC) * HIDDEN + int64_t(HIDDEN) * HC;
+}
+
+// W_Q^T [F][HC] and W_1^T [F+HC][HIDDEN] so that consecutive threads read consecutive
+// outputs, and the cross-attention columns of W_1 as bf16 hi [HIDDEN][HC] then lo,
+// each 32-wide head block in the MFMA k order of perm32.
+__device__ __forceinline__ void res_transpose_item(int64_t i, const float *__restrict__ blob,
+                                                   float *__restrict__ shared, int D) {
+  const ResLayout lay(D);
+  const int64_t F = 3 * D + 1;
+  const int64_t nq = F * HC, n1 = (F + HC) * HIDDEN, nc = int64_t(HIDDEN) * HC;
+  float *wqT = shared;
+  float *w1T = shared + align64f(F * HC);
+  uint16_t *w1c = reinterpret_cast<uint16_t *>(w1T + align64f((F + HC) * HIDDEN));
+  if (i < nq) {
+    const int64_t in = i / HC, o = i - in * HC;
+    wqT[i] = blob[lay.WQ + o * F + in];
+  } else if (i < nq + n1) {
+    const int64_t k = i - nq;
+    const int64_t in = k / HIDDEN, o = k - in * HIDDEN;
+    w1T[k] = blob[lay.W1 + o * (F + HC) + in];
+  } else if (i < nq + n1 + nc) {
+    const int64_t k = i - nq - n1;
+    const int64_t o = k / HC, c = k - o * HC;
+    const float v = blob[lay.W1 + o * (F + HC) + F + c];
+    const uint16_t hi = float_to_bf16_bits(v);
+    const int64_t at = o * HC + (c & ~int64_t(31)) + perm32_inv(int(c & 31));
+    w1c[at] = hi;
+    w1c[nc + at] = float_to_bf16_bits(v - bf16_bits_to_float(hi));
+  }
+}
+
+// Partial column sums of session b's memory rows (vector-unit layout), by a workgroup of 256
+// threads: part p sums rows [p*rows/P, (p+1)*rows/P).
+template <int D>
+__device__ __forceinline__ void mbar_part_wg(int b, int p, const ikv_session *__restrict__ sess,
+                                             const float *__restrict__ M, float *__restrict__ ws, int L, int Hkv) {
+  const ikv_session s = sess[b];
+  if (s.N <= s.C) return;
+  const int units = L * Hkv;
+  const int64_t rows = int64_t(units) * s.R;
+  const int64_t r0 = rows * p / MBAR_PARTS, r1 = rows * (p + 1) / MBAR_PARTS;
+  __shared__ float red[256 / D][D];
+  const int d = threadIdx.x % D, g = threadIdx.x / D;
+  constexpr int NG = 256 / D;
+  float a = 0.f;
+  for (int64_t r = r0 + g; r < r1; r += NG) a += M[s.mem_off + r * D + d];
+  red[g][d] = a;
+  __syncthreads();
+  if (g == 0) {
+    float t = 0.f;
+    for (int k = 0; k < NG; ++k) t += red[k][d];
+    const ScoreSizes z = score_sizes(s, L, units, D, true, false);
+    float *misc = ws + score_offset(sess, b, L, units, D, true, false) + z.off_misc();
+    misc[int64_t(p) * D + d] = t;
+  }
+}
+
 }  // namespace ikv
