@@ -1233,7 +1233,8 @@ k_score_stats(const uint16_t *__restrict__ kpool, int64_t num_slots, int L, int 
       for (int rb = 0; rb < 2; ++rb) {
         const float d = Zr[rb] != 0.f ? fmaxf(mx[rb], 0.f) : mx[rb] == -INFINITY ? 0.f : mx[rb];
         Mr[rb] += d;
-        Zr[rb] *= ex2(-d);
+        // an empty sum stays empty: a first reference far below zero makes exp2(-d) infinite
+        Zr[rb] = Zr[rb] != 0.f ? Zr[rb] * ex2(-d) : 0.f;
 #pragma unroll
         for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
