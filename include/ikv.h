@@ -282,11 +282,13 @@ ikv_status ikv_redirect_slots(const ikv_session *sess, const ikv_session *sess_d
  *   q, out: device [B][L][Hq][D] of the pool's kv_dtype (out rounded to nearest
  *   even). live, n_live: device, as written by ikv_redirect_slots;
  *   n_live[b] must not exceed sess[b].N.
- *   The live lists are split across workgroups by a bound known on the host,
- *   min(N, max(C, pi + qe - qs)) over the sessions (what a retention event leaves
- *   live), and by the number of (session, layer, KV head group) units, so that the
- *   workgroups fill about one resident round; a longer list is still attended
- *   exactly, with longer splits.
+ *   The live lists are split across workgroups by bounds known on the host,
+ *   min(N, max(C, pi + qe - qs)) per session (what a retention event leaves live), and
+ *   by the number of (session, layer, KV head group) units, so that the workgroups fill
+ *   their rounds on the chip; a longer list is still attended exactly, with longer
+ *   splits. Every session of a call gets the same number of splits: the order of a
+ *   session's sums, and so the rounding of its output, depends on the bounds of the
+ *   whole batch, not on the live counts.
  */
 ikv_status ikv_decode_attend_slotmap(const ikv_pool *pool, const ikv_session *sess,
                                      const ikv_session *sess_dev, int32_t B,

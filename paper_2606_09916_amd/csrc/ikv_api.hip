@@ -136,7 +136,7 @@ size_t redirect_bytes(int64_t num_slots, int B) {
 }
 
 size_t decode_bytes(const ikv_pool *p, const ikv_session *s, int B) {
-  return size_t(ikv::decode_plan(*p, s, B).parts) * p->L * p->Hq * size_t(ikv::decode_part_floats(p->D)) *
+  return size_t(B) * p->L * p->Hq * ikv::decode_splits(*p, s, B) * size_t(ikv::decode_part_floats(p->D)) *
          sizeof(float);
 }
 
@@ -592,14 +592,14 @@ ikv_status ikv_decode_attend_slotmap(const ikv_pool *pool, const ikv_session *se
   if (B == 0) return ok();
   if (!q || !live || !n_live || !out) return fail(IKV_EINVAL, "q / live / n_live / out is NULL");
   if ((r = check_ws(workspace, workspace_bytes, decode_bytes(pool, sess, B)))) return r;
-  const ikv::DecodePlan plan = ikv::decode_plan(*pool, sess, B);
+  const int splits = ikv::decode_splits(*pool, sess, B);
   if (debug_mode())
     for (int b = 0; b < B; ++b) {
       int64_t nl = 0;
       if ((r = debug_count(n_live, b, sess[b].N, (hipStream_t)stream, "n_live", &nl))) return r;
       if ((r = debug_ids(live, sess[b].slot_off, nl, 0, pool->num_slots, (hipStream_t)stream, "live", b))) return r;
     }
-  return hip_status(ikv::launch_decode(*pool, sess_dev, B, plan, q, live, n_live, out,
+  return hip_status(ikv::launch_decode(*pool, sess_dev, B, splits, q, live, n_live, out,
                                        static_cast<float *>(workspace), (hipStream_t)stream),
                     "ikv_decode_attend_slotmap");
 }

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "decode_plan.hpp"
 #include "ikv.h"
 #include "ikv_error.hpp"
 
@@ -161,8 +162,7 @@ inline int stats_chunk(int maxN, int head_pairs) {
 __host__ __device__ inline int64_t bitset_words(int64_t num_slots) { return align64f(cdiv(num_slots, 32)); }
 
 // Decode workspace: per (session, layer, query head, split) the partial (m, l, o[D]),
-// stored as all the o rows ([part][D]) followed by all the (m, l) pairs ([part][2]). A
-// session's parts follow those of the sessions before it, split fastest.
+// stored as all the o rows ([part][D]) followed by all the (m, l) pairs ([part][2]).
 __host__ __device__ inline int64_t decode_part_floats(int D) { return D + 2; }
 
 // ---------------------------------------------------------------- storage
@@ -281,15 +281,7 @@ size_t select_workspace_bytes(const ikv_session *sess, int B, int64_t total_posi
 hipError_t launch_redirect(const ikv_session *sess_dev, int B, int64_t num_slots, int32_t *slot_maps,
                            int32_t dead, const uint8_t *keep, int32_t *freed, int32_t *n_freed,
                            int32_t *live, int32_t *n_live, uint32_t *ws, hipStream_t st);
-// How a decode call splits the live lists: `cap` splits of a session at most (the grid), and
-// with several sessions `total` splits shared out by their live counts; `parts` bounds the
-// splits of the call (the workspace).
-struct DecodePlan {
-  int cap, total;
-  int64_t parts;
-};
-DecodePlan decode_plan(const ikv_pool &p, const ikv_session *sess_host, int B);
-hipError_t launch_decode(const ikv_pool &pool, const ikv_session *sess_dev, int B, const DecodePlan &plan,
+hipError_t launch_decode(const ikv_pool &pool, const ikv_session *sess_dev, int B, int splits,
                          const void *q, const int32_t *live, const int32_t *n_live, void *out,
                          float *ws, hipStream_t st);
 

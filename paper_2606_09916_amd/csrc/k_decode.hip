@@ -21,105 +21,6 @@
 
 namespace ikv {
 
-// Adjacent KV heads that a workgroup of the decode kernel takes (the head-group kernel: 4, 2
-// or 1; otherwise 1).
-static int decode_heads_per_wg(const ikv_pool &p) {
-  if (p.kv_dtype != IKV_BF16 || p.D != 128) return 1;
-  return p.Hkv % 4 == 0 ? 4 : (p.Hkv % 2 == 0 ? 2 : 1);
-}
-
-// An upper bound on the live positions a session holds after a retention event: the forced
-// set (at most pi + qe - qs positions) plus the budget, and never more than N. A slot map
-// that was never pruned may hold more; the decode is then still exact, only with longer
-// splits.
-static int64_t live_bound(const ikv_session &s) {
-  const int64_t forced = int64_t(std::max(0, s.pi)) + std::max(0, s.qe - s.qs);
-  return std::max<int64_t>(1, std::min<int64_t>(s.N, std::max<int64_t>(s.C, forced)));
-}
-
-// Splits of the live lists. One session: enough workgroups for about one resident round
-// (512: two per CU on the 256 CUs of MI355X), at least 64 live positions per split, at most
-// 64 splits. A workgroup ends with its split's stores, and its slot takes no new work until
-// they are done; long splits in one round pay that once per slot. At the Qwen3-8B 32k step
-// (8192 live, 72 units) that is 7 splits of 1171 positions: the head-group kernel 196 us
-// against 212 with 32 splits of 256 (without the stores, 32 splits ran in 191).
-//
-// Several sessions: a session's splits follow its own live count, out of `total` splits for
-// all of them: one round's where those come out even (no split more than 1.4 times the mean;
-// eight sessions of 4160, 48 layers of 4 KV heads, one split each: 535 us, 588 in three
-// rounds), else up to eight rounds of splits of about 1 k positions. With one split per
-// session, 16 sessions of 1158 to 8192 live positions (768 workgroups) waited on the longest:
-// 1754 us, 1511 in eight rounds.
-constexpr int DEC_ROUND = 512;                     // workgroups of one resident round
-constexpr int DEC_MAX_SPLITS = 64;                 // of one session
-constexpr int DEC_SPLIT_POS = 1024;                // positions per split of a call of several rounds
-constexpr int DEC_MAX_ROUNDS = 8;
-
-DecodePlan decode_plan(const ikv_pool &p, const ikv_session *sess_host, int B) {
-  const int64_t units = std::max<int64_t>(1, int64_t(p.L) * (p.Hkv / decode_heads_per_wg(p)));
-  int64_t longest = 1, sum = 0;
-  for (int b = 0; b < B; ++b) {
-    const int64_t n = live_bound(sess_host[b]);
-    longest = std::max(longest, n);
-    sum += n;
-  }
-  const auto clamp = [&](int64_t s) {
-    s = std::min<int64_t>(s, cdiv(longest, 64));
-    return int(s < 1 ? 1 : (s > DEC_MAX_SPLITS ? DEC_MAX_SPLITS : s));
-  };
-  DecodePlan d;
-  if (B <= 1) {
-    d.cap = d.total = clamp(DEC_ROUND / units);
-    d.parts = int64_t(B) * d.cap;
-    return d;
-  }
-  const int64_t even = sum * units / DEC_ROUND;    // positions per split of a single round
-  const int64_t one = DEC_ROUND / units;           // splits of a single round
-  int64_t need = 0, widest = 0;
-  for (int b = 0; b < B; ++b) {
-    const int64_t n = live_bound(sess_host[b]), k = std::max<int64_t>(1, n * one / sum);
-    need += k;
-    widest = std::max(widest, cdiv(n, k));
-  }
-  const bool fits = need <= one && 5 * widest <= 7 * even;
-  const int64_t rounds =
-      fits ? 1
-           : std::max<int64_t>(1, std::min<int64_t>(DEC_MAX_ROUNDS, (even + DEC_SPLIT_POS / 2) / DEC_SPLIT_POS));
-  d.total = int(std::max<int64_t>(1, DEC_ROUND * rounds / units));
-  d.cap = clamp(cdiv(longest * d.total, sum) + 1);
-  d.parts = std::min<int64_t>(int64_t(B) * d.cap, int64_t(d.total) + B);
-  return d;
-}
-
-// The splits of session b and the splits of the sessions before it, from the live counts.
-// They add up to at most total + B: each session rounds its share down, but takes one at
-// least. Every thread of the workgroup must call it; the decode and its merge get the same
-// values.
-struct DecodeSplits {
-  int n, before;
-};
-__device__ __forceinline__ DecodeSplits decode_share(const ikv_session *__restrict__ sess,
-                                                     const int32_t *__restrict__ n_live, int B, int b, int cap,
-                                                     int total) {
-  if (B == 1) return {cap, 0};
-  const int lane = threadIdx.x & 63;
-  auto count = [&](int i) { return max(0, min(n_live[i], sess[i].N)); };
-  double sum = 0.0;
-  for (int i = lane; i < B; i += WAVE) sum += count(i);
-#pragma unroll
-  for (int o = 1; o < WAVE; o <<= 1) sum += __shfl_xor(sum, o, WAVE);
-  auto share = [&](int i) {
-    const int n = count(i);
-    const int s = sum > 0.0 ? int(double(n) * double(total) / sum) : 0;
-    return max(1, min(min(s, cap), int(cdiv(n, 64))));
-  };
-  int before = 0;
-  for (int i = lane; i < b; i += WAVE) before += share(i);
-#pragma unroll
-  for (int o = 1; o < WAVE; o <<= 1) before += __shfl_xor(before, o, WAVE);
-  return {__builtin_amdgcn_readfirstlane(share(b)), __builtin_amdgcn_readfirstlane(before)};
-}
-
 // 8 consecutive elements kept as raw 16-byte words until they are used.
 template <typename T> struct Raw8 {
   static constexpr int W = sizeof(T) / 2;      // uint4 words: 1 for bf16, 2 for float
@@ -149,7 +50,7 @@ template <typename T> struct Raw8 {
 template <int D, int G>
 __device__ __forceinline__ void decode_finish(float (&m)[G], float (&lsum)[G], float (&o)[G][8], float (&red)[4][G][2],
                                               float (&ored)[4][G][D], float *__restrict__ ws, float *__restrict__ ws_ml,
-                                              int64_t part0, int l, int Hq, int g, int split, int nsplit) {
+                                              int b, int L, int l, int Hq, int g, int split, int nsplit) {
   constexpr int LPR = D / 8;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int rq = lane / LPR, cq = lane % LPR;
@@ -180,7 +81,7 @@ __device__ __forceinline__ void decode_finish(float (&m)[G], float (&lsum)[G], f
   __syncthreads();
   for (int e = t; e < G * (D + 2); e += 256) {
     const int h = e / (D + 2), d = e - h * (D + 2);
-    const int64_t part = part0 + (int64_t(l) * Hq + g * G + h) * nsplit + split;
+    const int64_t part = ((int64_t(b) * L + l) * Hq + g * G + h) * nsplit + split;
     float mm = -INFINITY;
     for (int k = 0; k < 4; ++k) mm = fmaxf(mm, red[k][h][0]);
     if (d == 0) {
@@ -201,8 +102,8 @@ __global__ void __launch_bounds__(256) k_decode_split(const T *__restrict__ kpoo
                                                       int64_t num_slots, int L, int Hkv,
                                                       const ikv_session *__restrict__ sess, const T *__restrict__ q,
                                                       const int32_t *__restrict__ live,
-                                                      const int32_t *__restrict__ n_live, int total,
-                                                      float *__restrict__ ws, float *__restrict__ ws_ml) {
+                                                      const int32_t *__restrict__ n_live, float *__restrict__ ws,
+                                                      float *__restrict__ ws_ml) {
   constexpr int LPR = D / 8;           // lanes per value row (8 channels each)
   constexpr int RPI = WAVE / LPR;      // value rows per load instruction
   __shared__ float qs[G][D];
@@ -214,11 +115,7 @@ __global__ void __launch_bounds__(256) k_decode_split(const T *__restrict__ kpoo
   const ikv_session s = sess[b];
   const int Hq = Hkv * G;
   const int u = blockIdx.y, l = u / Hkv, g = u - l * Hkv;
-  const int split = blockIdx.x;
-  const DecodeSplits sp = decode_share(sess, n_live, gridDim.z, b, gridDim.x, total);
-  const int nsplit = sp.n;
-  if (split >= nsplit) return;
-  const int64_t part0 = int64_t(sp.before) * L * Hq;
+  const int split = blockIdx.x, nsplit = gridDim.x;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   int n = n_live[b];
   n = n < 0 ? 0 : (n > s.N ? s.N : n);
@@ -315,7 +212,7 @@ __global__ void __launch_bounds__(256) k_decode_split(const T *__restrict__ kpoo
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
-  decode_finish<D, G>(m, lsum, o, red, ored, ws, ws_ml, part0, l, Hq, g, split, nsplit);
+  decode_finish<D, G>(m, lsum, o, red, ored, ws, ws_ml, b, L, l, Hq, g, split, nsplit);
 }
 
 typedef __bf16 bf16x8_d __attribute__((ext_vector_type(8)));
@@ -344,8 +241,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
                                                       const uint16_t *__restrict__ vpool, int64_t num_slots, int L,
                                                       int Hkv, int hpw, const ikv_session *__restrict__ sess,
                                                       const uint16_t *__restrict__ q, const int32_t *__restrict__ live,
-                                                      const int32_t *__restrict__ n_live, int total,
-                                                      float *__restrict__ ws, float *__restrict__ ws_ml) {
+                                                      const int32_t *__restrict__ n_live, float *__restrict__ ws,
+                                                      float *__restrict__ ws_ml) {
   constexpr int D = 128;
   constexpr int HB = G <= 4 ? 32 : 16; // live slots per half (fewer where the G output rows take the registers)
   constexpr int LPR = D / 8;           // lanes per value row (8 channels each)
@@ -363,11 +260,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
   const int t = threadIdx.x, lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int l = blockIdx.y / ngrp, g = (blockIdx.y - l * ngrp) * hpw + w;
-  const int split = blockIdx.x;
-  const DecodeSplits sp = decode_share(sess, n_live, gridDim.z, b, gridDim.x, total);
-  const int nsplit = sp.n;
-  if (split >= nsplit) return;
-  const int64_t part0 = int64_t(sp.before) * L * Hq;
+  const int split = blockIdx.x, nsplit = gridDim.x;
   const int gq = lane >> 4, r16 = lane & 15;
   const int rq = lane / LPR, cq = lane % LPR;     // value row group, channel group
   int n = n_live[b];
@@ -557,7 +450,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
   if (lane < LPR) {
 #pragma unroll
     for (int h = 0; h < G; ++h) {
-      const int64_t part = part0 + (int64_t(l) * Hq + g * G + h) * nsplit + split;
+      const int64_t part = ((int64_t(b) * L + l) * Hq + g * G + h) * nsplit + split;
       float4 *p = reinterpret_cast<float4 *>(ws + part * D + cq * 8);   // 32 aligned bytes per lane
       p[0] = make_float4(o[h][0], o[h][1], o[h][2], o[h][3]);
       p[1] = make_float4(o[h][4], o[h][5], o[h][6], o[h][7]);
@@ -572,25 +465,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 // the largest split maximum, out = sum_k o_k e^(m_k - M) / sum_k l_k e^(m_k - M).
 // An empty split (m = -inf) weighs zero; a row with no live position gives 0.
 template <typename T, int D>
-__global__ void __launch_bounds__(D) k_decode_combine(const ikv_session *__restrict__ sess,
-                                                      const int32_t *__restrict__ n_live, int cap, int total,
-                                                      const float *__restrict__ ws, const float *__restrict__ ws_ml,
-                                                      int L, int Hq, T *__restrict__ out) {
+__global__ void __launch_bounds__(D) k_decode_combine(const float *__restrict__ ws, const float *__restrict__ ws_ml,
+                                                      int nsplit, int L, int Hq, T *__restrict__ out) {
   constexpr int SMAX = DEC_MAX_SPLITS;
   constexpr int NW = D / 64;
   __shared__ float sm[SMAX], sl[SMAX], wm[NW];
   const int64_t row = int64_t(blockIdx.y) * L * Hq + blockIdx.x;
-  const DecodeSplits sp = decode_share(sess, n_live, gridDim.y, blockIdx.y, cap, total);
-  const int nsplit = sp.n;
-  const int64_t part = int64_t(sp.before) * L * Hq + int64_t(blockIdx.x) * nsplit;
-  const float *p = ws + part * D;
+  const float *p = ws + row * nsplit * D;
   const int d = threadIdx.x;
   float ok[SMAX];
 #pragma unroll
   for (int k = 0; k < SMAX; ++k) ok[k] = k < nsplit ? p[k * D + d] : 0.f;
   float mk = -INFINITY;
   if (d < nsplit) {
-    const float2 x = reinterpret_cast<const float2 *>(ws_ml + part * 2)[d];
+    const float2 x = reinterpret_cast<const float2 *>(ws_ml + row * nsplit * 2)[d];
     mk = x.x;
     sm[d] = mk;
     sl[d] = x.y;
@@ -615,60 +503,59 @@ __global__ void __launch_bounds__(D) k_decode_combine(const ikv_session *__restr
 }
 
 template <typename T, int D, int G>
-static hipError_t launch_decode_g(const ikv_pool &p, const ikv_session *sess_dev, int B, const DecodePlan &plan, const void *q,
+static hipError_t launch_decode_g(const ikv_pool &p, const ikv_session *sess_dev, int B, int splits, const void *q,
                                   const int32_t *live, const int32_t *n_live, void *out, float *ws, hipStream_t st) {
   // split state: the output rows of every (session, layer, query head, split) first,
   // [part][D], then their (max, sum) pairs, [part][2]
-  float *ws_ml = ws + plan.parts * p.L * p.Hq * D;
+  float *ws_ml = ws + int64_t(B) * p.L * p.Hq * splits * D;
   if constexpr (sizeof(T) == 2 && D == 128) {
     const int hpw = decode_heads_per_wg(p);
-    const dim3 grid(plan.cap, p.L * (p.Hkv / hpw), B);
+    const dim3 grid(splits, p.L * (p.Hkv / hpw), B);
     KTimer kt_("k_decode_heads<G>", st);
     if (p.num_slots * p.Hkv * D * 2 < (int64_t(1) << 32))
       k_decode_heads<G, true><<<grid, 64 * hpw, 0, st>>>((const uint16_t *)p.k_pool, (const uint16_t *)p.v_pool,
                                                          p.num_slots, p.L, p.Hkv, hpw, sess_dev, (const uint16_t *)q,
-                                                         live, n_live, plan.total, ws, ws_ml);
+                                                         live, n_live, ws, ws_ml);
     else
       k_decode_heads<G, false><<<grid, 64 * hpw, 0, st>>>((const uint16_t *)p.k_pool, (const uint16_t *)p.v_pool,
                                                           p.num_slots, p.L, p.Hkv, hpw, sess_dev, (const uint16_t *)q,
-                                                          live, n_live, plan.total, ws, ws_ml);
+                                                          live, n_live, ws, ws_ml);
   } else {
     KTimer kt_("k_decode_split<T, D, G>", st);
-    k_decode_split<T, D, G><<<dim3(plan.cap, p.L * p.Hkv, B), 256, 0, st>>>(
-        (const T *)p.k_pool, (const T *)p.v_pool, p.num_slots, p.L, p.Hkv, sess_dev, (const T *)q, live, n_live,
-        plan.total, ws, ws_ml);
+    k_decode_split<T, D, G><<<dim3(splits, p.L * p.Hkv, B), 256, 0, st>>>(
+        (const T *)p.k_pool, (const T *)p.v_pool, p.num_slots, p.L, p.Hkv, sess_dev, (const T *)q, live, n_live, ws,
+        ws_ml);
   }
   {
     KTimer kt_("k_decode_combine<T, D>", st);
-    k_decode_combine<T, D><<<dim3(p.L * p.Hq, B), D, 0, st>>>(sess_dev, n_live, plan.cap, plan.total, ws, ws_ml,
-                                                                    p.L, p.Hq, (T *)out);
+    k_decode_combine<T, D><<<dim3(p.L * p.Hq, B), D, 0, st>>>(ws, ws_ml, splits, p.L, p.Hq, (T *)out);
   }
   return hipGetLastError();
 }
 
 template <typename T, int D>
-static hipError_t launch_decode_d(const ikv_pool &p, const ikv_session *sd, int B, const DecodePlan &plan, const void *q,
+static hipError_t launch_decode_d(const ikv_pool &p, const ikv_session *sd, int B, int splits, const void *q,
                                   const int32_t *live, const int32_t *n_live, void *out, float *ws, hipStream_t st) {
   switch (p.Hq / p.Hkv) {
-    case 1: return launch_decode_g<T, D, 1>(p, sd, B, plan, q, live, n_live, out, ws, st);
-    case 2: return launch_decode_g<T, D, 2>(p, sd, B, plan, q, live, n_live, out, ws, st);
-    case 3: return launch_decode_g<T, D, 3>(p, sd, B, plan, q, live, n_live, out, ws, st);
-    case 4: return launch_decode_g<T, D, 4>(p, sd, B, plan, q, live, n_live, out, ws, st);
-    case 5: return launch_decode_g<T, D, 5>(p, sd, B, plan, q, live, n_live, out, ws, st);
-    case 6: return launch_decode_g<T, D, 6>(p, sd, B, plan, q, live, n_live, out, ws, st);
-    case 7: return launch_decode_g<T, D, 7>(p, sd, B, plan, q, live, n_live, out, ws, st);
-    default: return launch_decode_g<T, D, 8>(p, sd, B, plan, q, live, n_live, out, ws, st);
+    case 1: return launch_decode_g<T, D, 1>(p, sd, B, splits, q, live, n_live, out, ws, st);
+    case 2: return launch_decode_g<T, D, 2>(p, sd, B, splits, q, live, n_live, out, ws, st);
+    case 3: return launch_decode_g<T, D, 3>(p, sd, B, splits, q, live, n_live, out, ws, st);
+    case 4: return launch_decode_g<T, D, 4>(p, sd, B, splits, q, live, n_live, out, ws, st);
+    case 5: return launch_decode_g<T, D, 5>(p, sd, B, splits, q, live, n_live, out, ws, st);
+    case 6: return launch_decode_g<T, D, 6>(p, sd, B, splits, q, live, n_live, out, ws, st);
+    case 7: return launch_decode_g<T, D, 7>(p, sd, B, splits, q, live, n_live, out, ws, st);
+    default: return launch_decode_g<T, D, 8>(p, sd, B, splits, q, live, n_live, out, ws, st);
   }
 }
 
-hipError_t launch_decode(const ikv_pool &p, const ikv_session *sess_dev, int B, const DecodePlan &plan, const void *q,
+hipError_t launch_decode(const ikv_pool &p, const ikv_session *sess_dev, int B, int splits, const void *q,
                          const int32_t *live, const int32_t *n_live, void *out, float *ws, hipStream_t st) {
   const bool bf = p.kv_dtype == IKV_BF16;
   if (p.D == 128)
-    return bf ? launch_decode_d<uint16_t, 128>(p, sess_dev, B, plan, q, live, n_live, out, ws, st)
-              : launch_decode_d<float, 128>(p, sess_dev, B, plan, q, live, n_live, out, ws, st);
-  return bf ? launch_decode_d<uint16_t, 64>(p, sess_dev, B, plan, q, live, n_live, out, ws, st)
-            : launch_decode_d<float, 64>(p, sess_dev, B, plan, q, live, n_live, out, ws, st);
+    return bf ? launch_decode_d<uint16_t, 128>(p, sess_dev, B, splits, q, live, n_live, out, ws, st)
+              : launch_decode_d<float, 128>(p, sess_dev, B, splits, q, live, n_live, out, ws, st);
+  return bf ? launch_decode_d<uint16_t, 64>(p, sess_dev, B, splits, q, live, n_live, out, ws, st)
+            : launch_decode_d<float, 64>(p, sess_dev, B, splits, q, live, n_live, out, ws, st);
 }
 
 }  // namespace ikv

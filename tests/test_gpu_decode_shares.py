@@ -1,5 +1,5 @@
-"""Decode of several sessions of uneven live counts: the splits are shared out by the live
-counts on the device, so their number and the layout of the split state differ per session.
+"""Decode of several sessions of uneven live counts: every session has the same number of
+splits, chosen from the bounds known on the host, so that short lists leave splits empty.
 Against float64 attention; a bf16 output is at most half a unit in the last place (2^-9 of
 its value) and the softmax's float32 rounding from it."""
 import numpy as np
@@ -11,10 +11,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype,L,Hkv,G,D,bound,counts", [
-    ("bf16", 2, 4, 5, 128, 9000, (9000, 1, 700, 64, 0, 65, 4097)),        # one round, an empty session
+    ("bf16", 2, 4, 5, 128, 9000, (9000, 1, 700, 64, 0, 65, 4097)),        # an empty session
     ("bf16", 2, 2, 4, 128, 300, (2999, 3000, 17)),                        # live lists past the budget's bound
-    ("bf16", 48, 4, 2, 128, 6000, (6000, 1200, 5999, 31, 4000, 2500, 3333, 100, 2)),   # several rounds
-    ("bf16", 40, 1, 8, 128, 40, (40,) * 70 + (3,) * 2),                   # more sessions than lanes of a wave
+    ("bf16", 48, 4, 2, 128, 6000, (6000, 1200, 5999, 31, 4000, 2500, 3333, 100, 2)),   # seven splits, some empty
+    ("bf16", 40, 1, 8, 128, 40, (40,) * 70 + (3,) * 2),                   # many sessions of one split
     ("f32", 1, 2, 4, 64, 4000, (4000, 0, 128, 129, 1000)),
     ("f32", 1, 1, 1, 64, 70, (0, 0, 0)),                                  # nothing live at all
 ])
