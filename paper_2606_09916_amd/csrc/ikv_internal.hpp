@@ -115,8 +115,11 @@ __host__ __device__ inline ScoreSizes score_sizes(const ikv_session &s, int L, i
   ScoreSizes z;
   z.msplit = mfma ? align64f(int64_t(units) * pad16(s.R) * 128) : 0;
   // MFMA: 64-position partials, or (one key pass) one per 32 list entries, at most N / 32 +
-  // 32 of them for chunks of up to 1024 positions
-  z.part = mfma ? align64f((s.R <= STASH_MAX_R ? cdiv(s.N, 32) + 36 : cdiv(s.N, PART_TILE) + 8) * units * s.R * 2)
+  // 32 of them for chunks of up to 1024 positions. One product for both: every workgroup adds
+  // up the sizes of the sessions before its own in scalar registers, and with two the first
+  // score pass spilled three of them (8 sessions of up to 3981 positions, 192 units, 83 rows:
+  // 467 us, 446 like this).
+  z.part = mfma ? align64f((cdiv(s.N, PART_TILE) + 18) * units * (s.R <= STASH_MAX_R ? 4 * s.R : 2 * s.R))
                 : align64f(int64_t(units) * s.R * cdiv(s.N, SCORE_TILE) * 2);
   z.lse = align64f(int64_t(units) * s.R * (mfma ? 3 : 2));
   z.lse_pairs = int64_t(units) * s.R * 2;

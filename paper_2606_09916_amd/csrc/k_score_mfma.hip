@@ -1348,13 +1348,14 @@ __device__ __forceinline__ float2 merge_quarters(const float2 (&v)[4], int left)
 // first pass: with `kv` (the matrix-core head) RES_KEYS workgroups build K' and V' of
 // one live query row each from the keys (res_kv_keys_wg) and `nfold` fold the first
 // layer (res_fold_wg), then one workgroup writes mbar and the live query positions
-// (res_setup_body).
+// (res_setup_body). QUARTERS: the partials are those of the narrow-tile key pass.
+template <bool QUARTERS>
 __global__ void __launch_bounds__(512) k_lse_mfma(const ikv_session *__restrict__ sess, float *__restrict__ ws, int L,
                                                   int Hkv, bool resid, int ptile, int pper,
                                                   const int32_t *__restrict__ slot_maps,
                                                   const int32_t *__restrict__ qpos, int dead, bool pairs, bool kv,
                                                   int nfold, const uint16_t *__restrict__ kpool, int64_t num_slots,
-                                                  const float *__restrict__ blob, float *__restrict__ shared, bool quarters) {
+                                                  const float *__restrict__ blob, float *__restrict__ shared) {
   __shared__ float sm[8][64], sz[8][64];
   const int b = blockIdx.y;
   const int nkv = kv ? RES_KEYS : 0;
@@ -1376,24 +1377,24 @@ __global__ void __launch_bounds__(512) k_lse_mfma(const ikv_session *__restrict_
   const int64_t rows = int64_t(units) * s.R;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   // 64 rows per workgroup; 16 with quarter partials (four times the bytes), four lanes per row
-  const int rpw = quarters ? 16 : 64, qe = quarters ? lane >> 4 : 0;
-  const int64_t i = int64_t(bx) * rpw + (quarters ? lane & 15 : lane);
+  const int rpw = QUARTERS ? 16 : 64, qe = QUARTERS ? lane >> 4 : 0;
+  const int64_t i = int64_t(bx) * rpw + (QUARTERS ? lane & 15 : lane);
   if (int64_t(bx) * rpw >= rows) return;
   const bool on = i < rows;
   const ScoreSizes z = score_sizes(s, L, units, MD, resid, true);
   float *base = ws + score_offset(sess, b, L, units, MD, resid, true);
   const float *part = base + z.off_part();
   // partials: one per ptile positions, or pper per ptile-position chunk (list tiles), each
-  // list tile's four quarters apart where the narrow-tile pass left them (one per 32
-  // entries, those past the chunk's count not written)
+  // list tile's four quarters apart with QUARTERS (one per 32 entries, those past the
+  // chunk's count not written)
   const int64_t tiles = pper > 0 ? cdiv(s.N, ptile) * pper : cdiv(s.N, ptile);
   const int32_t *cc = reinterpret_cast<const int32_t *>(base + z.off_ccount(s.N));
   float m = -INFINITY, zs = 0.f;
   constexpr int LB = 8;                            // tiles in flight per thread
-  if (on || quarters)                              // quarters: the lanes of a row exchange their quarters
+  if (on || QUARTERS)                              // quarters: the lanes of a row exchange their quarters
     for (int64_t k0 = w; k0 < tiles; k0 += 8 * LB) {
       float2 pv[LB];
-      if (quarters) {
+      if (QUARTERS) {
         // lane group qe merges tiles q = qe and qe + 4, then the lanes of a row exchange them
         float2 v[2][4], mt[2];
 #pragma unroll
@@ -1666,9 +1667,9 @@ hipError_t launch_score_mfma(const ScoreArgs &a, hipStream_t st) {
     // the SnapKV-style score: row normalisers, the per-unit attention masses, the pool
     {
       KTimer kt_("k_lse_mfma", st);
-      k_lse_mfma<<<dim3(unsigned(cdiv(int64_t(units) * a.maxR, 64)), a.B), 512, 0, st>>>(
+      k_lse_mfma<false><<<dim3(unsigned(cdiv(int64_t(units) * a.maxR, 64)), a.B), 512, 0, st>>>(
           a.sess_dev, a.ws, p.L, p.Hkv, false, chunk, 0, a.slot_maps, a.qpos, p.dead_slot, true, false, 0, kp,
-          p.num_slots, a.residual, a.ws_shared, false);
+          p.num_slots, a.residual, a.ws_shared);
     }
     float *umass = a.ws_shared;                     // after the sessions' blocks
     {
@@ -1695,15 +1696,18 @@ hipError_t launch_score_mfma(const ScoreArgs &a, hipStream_t st) {
     // with the matrix-core residual head, this launch also folds its first layer (one
     // item of fold_items() per thread) and builds K', V'
     constexpr int FOLD_WGS = int((fold_items<MD>() + 511) / 512);
-    const bool quarters = a.stash && narrow > 0;
     const bool kv = a.mfma_resid;
     const int nfold = kv ? FOLD_WGS : 0;
     const int extra = resid ? (kv ? RES_KEYS : 0) + nfold + 1 : 0;
     KTimer kt_("k_lse_mfma", st);
-    k_lse_mfma<<<dim3(unsigned(cdiv(int64_t(units) * a.maxR, quarters ? 16 : 64) + extra), a.B), 512, 0, st>>>(
-        a.sess_dev, a.ws, p.L, p.Hkv, resid, stats ? chunk : a.stash ? lch : ring ? PART_TILE : MFMA_TILE,
-        a.stash ? lch / MFMA_TILE : 0, a.slot_maps, a.qpos, p.dead_slot, a.stats, kv, nfold, kp, p.num_slots,
-        a.residual, a.ws_shared, quarters);
+    auto run = [&](auto lse, int rows) {
+      lse<<<dim3(unsigned(cdiv(int64_t(units) * a.maxR, rows) + extra), a.B), 512, 0, st>>>(
+          a.sess_dev, a.ws, p.L, p.Hkv, resid, stats ? chunk : a.stash ? lch : ring ? PART_TILE : MFMA_TILE,
+          a.stash ? lch / MFMA_TILE : 0, a.slot_maps, a.qpos, p.dead_slot, a.stats, kv, nfold, kp, p.num_slots,
+          a.residual, a.ws_shared);
+    };
+    if (a.stash && narrow > 0) run(k_lse_mfma<true>, 16);
+    else run(k_lse_mfma<false>, 64);
   }
   if (a.stash)
     {
