@@ -615,6 +615,10 @@ def main() -> int:
         + (n_scored * sh.D * 4 if flags & ikv.IKV_RESIDUAL else 0),
         "k_score_stash": sum(a * units * R * 4 for R, a in zip(Rs, nA_b)) + nA * 4,
     }
+    # the same passes in narrow tiles (calls of few positions)
+    algo["k_score_narrow_once"] = algo["k_score_once"]
+    for flag in ("true", "false"):
+        algo[f"k_score_narrow<{flag}>"] = algo[f"k_score_ws<{flag}>"]
     kernels = {}
     for name, v in per_kernel.items():
         e = {"ms_per_step": round(sum(v) / args.steps, 4), "launches": len(v) // args.steps,

@@ -650,7 +650,7 @@ hipError_t launch_score_narrow(const ScoreArgs &a, int lch, int ng, hipStream_t 
   // one session: up to a round of workgroups, whichever width the kernel takes
   const int64_t tiles = a.B == 1 ? PW_CUS : cdiv(cdiv(a.maxN, 32), ng);
   const dim3 grid(unsigned(tiles), unsigned(a.B));
-  KTimer kt_(a.stash ? "k_score_once" : resid ? "k_score_ws<true>" : "k_score_ws<false>", st);
+  KTimer kt_(a.stash ? "k_score_narrow_once" : resid ? "k_score_narrow<true>" : "k_score_narrow<false>", st);
   if (a.stash) {
     if (resid) k_score_narrow<true, 1, true><<<grid, PW_THREADS, 0, st>>>(x);
     else k_score_narrow<false, 1, true><<<grid, PW_THREADS, 0, st>>>(x);
