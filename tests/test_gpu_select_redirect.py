@@ -164,12 +164,14 @@ def test_select_barrier_give_up_is_reported(dev, monkeypatch):
 
 
 @pytest.mark.parametrize("n,path", [(16384, "k_select_small"), (16385, "k_select_coop")])
-def test_select_one_workgroup_limit(dev, n, path):
-    """Both sides of the length up to which one workgroup per session selects; heavy ties."""
+def test_select_one_workgroup_limit(dev, monkeypatch, n, path):
+    """Both sides of the length up to which one workgroup per session selects; heavy ties.
+    Every MI355X launches cooperatively, so the longer call takes that path and no other."""
+    monkeypatch.delenv("IKV_NO_COOP", raising=False)
     ikv.timing(True)
     try:
         test_select_long_sessions_exact(dev, (n, 1025, 1), True)
         names = [name for name, _ in ikv.timing_read()]
     finally:
         ikv.timing(False)
-    assert path in names or (path == "k_select_coop" and "k_select_small" in names)
+    assert {name for name in names if name.startswith("k_select")} == {path}
