@@ -487,11 +487,6 @@ def main() -> int:
         del sg
         log(f"R = G = {sh.G}: {rows_per_head['value']:.0f} tokens/s, {g_ms:.3f} ms per step")
 
-    # The one-key-pass score with the normaliser exchange between resident workgroups is
-    # switched off in the library (a wrong row normaliser on some calls, cause not found),
-    # so its comparison field stays null.
-    one_pass = None
-
     # Layout ablation (Table 7): the compact apply path of the standard compactors on the
     # same kept set, left-packing the kept rows (keys re-rotated) into the slots the
     # redirect freed, against the redirect itself. One session only.
@@ -564,8 +559,6 @@ def main() -> int:
         nA_b.append(int(((Sb != st.dead) & ~forced).sum()) if scored(x) else 0)
         sc_b.append(scored(x))
     nA = sum(nA_b)
-    if one_pass is not None:
-        one_pass["gbs_keys_once"] = round(nA * sh.L * sh.Hkv * sh.D * 2 / (one_pass["score_ms"] / 1e3) / 1e9, 1)
     t_ss = (phase_ms[2] + phase_ms[3]) / 1e3
     tokens_per_s = nA / t_ss
 
@@ -596,9 +589,6 @@ def main() -> int:
         "k_score_ring": key_bytes + mem_bytes,
         "k_score_ws<true>": key_bytes + mem_bytes + n_scored * 4 + n_scored * sh.D * 4,
         "k_score_ws<false>": key_bytes + mem_bytes + n_scored * 4,
-        # the one key pass at 16 < R <= 64 (opt-in): what the second pass alone reads and writes
-        "k_score_fused": key_bytes + mem_bytes + n_scored * 4
-        + (n_scored * sh.D * 4 if flags & ikv.IKV_RESIDUAL else 0),
         "k_decode_split<T, D, G>": kv_live + q_rows,
         "k_decode_heads<G>": kv_live + q_rows,
         "k_qm_update<T, 128>": span_bytes,
@@ -661,7 +651,7 @@ def main() -> int:
         "wall_s_timed": round(wall, 3),
         "roofline": roofline,
         "kernels": kernels,
-        "rows_per_query_head": rows_per_head, "one_pass_exchange": one_pass,
+        "rows_per_query_head": rows_per_head,
         "layout_ablation": layout,
         "prefill_span": prefill,
     }
