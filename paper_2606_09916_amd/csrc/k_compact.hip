@@ -117,12 +117,15 @@ __device__ __forceinline__ cc_u32x4 cc_pack(const float (&y)[4]) {
   return v;
 }
 
-// A workgroup walks kept indices blockIdx.x, + gridDim.x, ... CC_WGS workgroups are two
-// rounds of eight per CU: one per position would send those past the kept count through the
-// chip to find that out. CC_U steps of 16-byte loads are in flight per thread, and the first
-// are issued before the angles, whose float64 pow, cos and sin take about as long as a
-// memory round trip.
-constexpr int CC_WGS = 4096;
+// A workgroup walks kept indices blockIdx.x, + gridDim.x, ... The registers hold three (bf16)
+// or four (float32) workgroups per CU, 768 or 1024 on the chip; the hardware hands out the
+// rest as they end. CC_WGS bounds the workgroups that come only to find no index, and is large
+// enough to balance: 36 layers of 8 KV heads, 8192 of 32,768 kept, 471 us with 512, 472 with
+// 1536 and 4096, 461 with 8192 and with one per position; 48 layers of 4, 16,000 of 60,000,
+// 640, 632, 624 and 625 with 512, 4096, 8192 and one per position. CC_U steps of 16-byte loads
+// are in flight per thread, and the first are issued before the angles, whose float64 pow, cos
+// and sin take about as long as a memory round trip.
+constexpr int CC_WGS = 8192;
 constexpr int CC_U = 3;
 
 template <typename T>
