@@ -47,9 +47,9 @@ inline int64_t decode_fill(int64_t n) { return 100 * n / ((n + DEC_ROUND - 1) / 
 // Several sessions that one round holds fewer than three splits of (calls of the head-group
 // kernel, us):
 //  - more splits where they fill their rounds better, up to four of at least 256 positions:
-//    8 x 72 units of 4096 positions 861 with one split, 762 with four; 16 x 48 units 1091 and
-//    1001 with two; where one split fills them, one is best (5 x 96 units: 667, 669 with two,
-//    1024 positions each: 188 and 191).
+//    8 x 72 units of 3000 positions 636 with one split, 574 with four; 16 x 48 units 817 and
+//    765 with two; where one split fills them, one is best (5 x 96 units of 2400 to 3000
+//    positions: 433, 438 with two; of 1200 to 1500: 239 and 247).
 //  - lists of uneven bounds (the longest 1.15 times the mean or more): up to eight splits of
 //    at least 768 positions in up to ten rounds, so that the last workgroups are short ones.
 //    5 x 96 units of 1200 to 12,000 positions 1402 with one split, 1155 with eight; 16 x 48
