@@ -114,15 +114,17 @@ __host__ __device__ inline ScoreSizes score_sizes(const ikv_session &s, int L, i
                                                   bool mfma) {
   ScoreSizes z;
   z.msplit = mfma ? align64f(int64_t(units) * pad16(s.R) * 128) : 0;
-  // MFMA: 64-position partials, or (one key pass) one per 32 list entries, at most N / 32 +
-  // 32 of them for chunks of up to 1024 positions. One product for both: every workgroup adds
-  // up the sizes of the sessions before its own in scalar registers, and with two the first
-  // score pass spilled three of them (8 sessions of up to 3981 positions, 192 units, 83 rows:
-  // 467 us, 446 like this).
-  z.part = mfma ? align64f((cdiv(s.N, PART_TILE) + 18) * units * (s.R <= STASH_MAX_R ? 4 * s.R : 2 * s.R))
-                : align64f(int64_t(units) * s.R * cdiv(s.N, SCORE_TILE) * 2);
-  z.lse = align64f(int64_t(units) * s.R * (mfma ? 3 : 2));
-  z.lse_pairs = int64_t(units) * s.R * 2;
+  // part, MFMA: 64-position partials, or (one key pass) one per 32 list entries, at most N / 32
+  // + 32 of them for chunks of up to 1024 positions: a shift apart, and sharing the row count
+  // with lse, since every workgroup adds up the sizes of the sessions before its own in scalar
+  // registers. With a count of partials for each form the first score pass spilled three of
+  // them (8 sessions of up to 3981 positions, 192 units, 83 rows: 467 us, 441 like this; 64
+  // sessions: 29.6 and 27.5 ms).
+  const int64_t rows = int64_t(units) * s.R;
+  z.part = mfma ? align64f(((cdiv(s.N, PART_TILE) + 18) * rows) << (s.R <= STASH_MAX_R ? 2 : 1))
+                : align64f(rows * cdiv(s.N, SCORE_TILE) * 2);
+  z.lse = align64f(rows * (mfma ? 3 : 2));
+  z.lse_pairs = rows * 2;
   z.rulep = mfma ? 0 : align64f(int64_t(L) * s.N);
   z.kbar = resid ? align64f(int64_t(s.N) * D) : 0;
   z.kq = resid ? align64f(int64_t(s.nq) * D) : 0;
@@ -134,7 +136,7 @@ __host__ __device__ inline ScoreSizes score_sizes(const ikv_session &s, int L, i
   z.kvf = resid && mfma ? align64f(KVF_BF16 / 2) : 0;
   z.mbp = resid && mfma ? align64f(int64_t(units / 2) * D) : 0;
   z.clist = mfma ? align64f(int64_t(s.N) + 1024) + align64f(cdiv(s.N, 128) + 1) : 0;
-  z.stash = mfma && s.R <= STASH_MAX_R ? int64_t(units) * s.R * stash_stride(s.N) : 0;
+  z.stash = mfma && s.R <= STASH_MAX_R ? rows * stash_stride(s.N) : 0;
   return z;
 }
 
