@@ -15,6 +15,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "ikv_internal.hpp"
 
@@ -122,13 +123,27 @@ __device__ __forceinline__ cc_u32x4 cc_pack(const float (&y)[4]) {
 // rest as they end. CC_WGS bounds the workgroups that come only to find no index, and is large
 // enough to balance: 36 layers of 8 KV heads, 8192 of 32,768 kept, 471 us with 512, 472 with
 // 1536 and 4096, 461 with 8192 and with one per position; 48 layers of 4, 16,000 of 60,000,
-// 640, 632, 624 and 625 with 512, 4096, 8192 and one per position. CC_U steps of 16-byte loads
+// 640, 632, 624 and 625 with 512, 4096, 8192 and one per position. U steps of 16-byte loads
 // are in flight per thread, and the first are issued before the angles, whose float64 pow, cos
 // and sin take about as long as a memory round trip.
 constexpr int CC_WGS = 8192;
-constexpr int CC_U = 3;
 
-template <typename T>
+// Steps in flight (one, two or three) and threads of a workgroup, for the `steps` of an index
+// (a step: 16 bytes of each half of a key row and of a value row): no more in flight than
+// there are, and every turn about full. Lanes past the last step read its rows again. With
+// three steps of 256 threads whatever the count, one layer of 2 KV heads (16 steps; 32
+// sessions, 2000 of 8000 kept) took 290 us, 75 like this; two layers of 8 (128 steps) 330 and
+// 171; from 36 layers of 8 (2304 steps) on the two are the same.
+struct CopyShape {
+  int u, threads;
+};
+inline CopyShape copy_shape(int64_t steps) {
+  const int u = steps <= CC_THREADS ? 1 : steps <= 2 * CC_THREADS ? 2 : 3;
+  const int64_t turns = cdiv(steps, u * CC_THREADS);
+  return {u, int(cdiv(cdiv(steps, turns * u), WAVE)) * WAVE};
+}
+
+template <typename T, int U>
 __global__ void __launch_bounds__(CC_THREADS) k_compact_copy(const ikv_session *__restrict__ sess, T *__restrict__ kp,
                                                              T *__restrict__ vp, int64_t num_slots, int L, int Hkv,
                                                              int D, const int32_t *__restrict__ slot_maps,
@@ -139,7 +154,7 @@ __global__ void __launch_bounds__(CC_THREADS) k_compact_copy(const ikv_session *
   __shared__ __align__(16) float cs[64], sn[64];
   const int b = blockIdx.y;
   const ikv_session s = sess[b];
-  const int h = D / 2, t = threadIdx.x;
+  const int h = D / 2, t = threadIdx.x, nt = blockDim.x;
   const int nk = n_keep[b];
   const int64_t row = int64_t(Hkv) * D;          // elements of one slot in one layer
   const int per = h / PP, groups = Hkv * per;    // pair groups per head and per layer
@@ -147,14 +162,14 @@ __global__ void __launch_bounds__(CC_THREADS) k_compact_copy(const ikv_session *
   for (int tk = blockIdx.x; tk < nk; tk += gridDim.x) {
     const int j = pos_list[s.slot_off + tk];
     const int64_t src = slot_maps[s.slot_off + j], dslot = dst[s.slot_off + tk];
-    cc_u32x4 k1[CC_U], k2[CC_U], v1[CC_U], v2[CC_U];
-    int64_t od[CC_U];
-    int q[CC_U];
+    cc_u32x4 k1[U], k2[U], v1[U], v2[U];
+    int64_t od[U];
+    int q[U];
     // steps past the last are clamped: they read its rows again and store nothing
     auto load = [&](int g0) __attribute__((always_inline)) {
 #pragma unroll
-      for (int u = 0; u < CC_U; ++u) {
-        const int g = min(g0 + u * CC_THREADS, steps - 1);
+      for (int u = 0; u < U; ++u) {
+        const int g = min(g0 + u * nt, steps - 1);
         const int l = g / groups, r = g - l * groups;
         const int hd = r / per;
         q[u] = (r - hd * per) * PP;
@@ -176,8 +191,8 @@ __global__ void __launch_bounds__(CC_THREADS) k_compact_copy(const ikv_session *
     __syncthreads();
     for (int g0 = t;;) {
 #pragma unroll
-      for (int u = 0; u < CC_U; ++u) {
-        if (g0 + u * CC_THREADS >= steps) continue;
+      for (int u = 0; u < U; ++u) {
+        if (g0 + u * nt >= steps) continue;
         float x1[PP], x2[PP], y1[PP], y2[PP];
         cc_unpack(k1[u], x1);
         cc_unpack(k2[u], x2);
@@ -192,7 +207,7 @@ __global__ void __launch_bounds__(CC_THREADS) k_compact_copy(const ikv_session *
         cc_st(vp + od[u], v1[u]);
         cc_st(vp + od[u] + h, v2[u]);
       }
-      g0 += CC_U * CC_THREADS;
+      g0 += U * nt;
       if (g0 >= steps) break;
       load(g0);
     }
@@ -212,14 +227,20 @@ hipError_t launch_compact(const ikv_pool &pool, const ikv_session *sess_dev, int
   if (maxN > 0) {
     KTimer kt_("k_compact_copy", st);
     const dim3 grid(unsigned(std::min(maxN, CC_WGS)), B);
-    if (pool.kv_dtype == IKV_BF16)
-      k_compact_copy<uint16_t><<<grid, CC_THREADS, 0, st>>>(
-          sess_dev, static_cast<uint16_t *>(pool.k_pool), static_cast<uint16_t *>(pool.v_pool), pool.num_slots, pool.L,
-          pool.Hkv, pool.D, slot_maps, dst, pos_list, n_keep, base);
-    else
-      k_compact_copy<float><<<grid, CC_THREADS, 0, st>>>(
-          sess_dev, static_cast<float *>(pool.k_pool), static_cast<float *>(pool.v_pool), pool.num_slots, pool.L,
-          pool.Hkv, pool.D, slot_maps, dst, pos_list, n_keep, base);
+    const bool bf = pool.kv_dtype == IKV_BF16;
+    const CopyShape c = copy_shape(int64_t(pool.L) * pool.Hkv * (pool.D / 2 / (bf ? CC_PP<uint16_t> : CC_PP<float>)));
+    auto run = [&](auto kernel, auto *kp, auto *vp) {
+      kernel<<<grid, c.threads, 0, st>>>(sess_dev, kp, vp, pool.num_slots, pool.L, pool.Hkv, pool.D, slot_maps, dst,
+                                         pos_list, n_keep, base);
+    };
+    auto pick = [&](auto *kp, auto *vp) {
+      using T = std::remove_pointer_t<decltype(kp)>;
+      if (c.u == 1) run(k_compact_copy<T, 1>, kp, vp);
+      else if (c.u == 2) run(k_compact_copy<T, 2>, kp, vp);
+      else run(k_compact_copy<T, 3>, kp, vp);
+    };
+    if (bf) pick(static_cast<uint16_t *>(pool.k_pool), static_cast<uint16_t *>(pool.v_pool));
+    else pick(static_cast<float *>(pool.k_pool), static_cast<float *>(pool.v_pool));
   }
   return hipGetLastError();
 }

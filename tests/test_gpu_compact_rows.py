@@ -12,7 +12,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype,L,Hkv,D,N", [("f32", 1, 1, 64, 40), ("f32", 3, 2, 64, 700), ("f32", 9, 8, 128, 300),
                                              ("bf16", 1, 1, 64, 33), ("bf16", 36, 8, 128, 129), ("bf16", 13, 8, 128, 90),
-                                             ("bf16", 2, 1, 128, 9500), ("bf16", 2, 1, 128, 12000)])
+                                             ("bf16", 2, 1, 128, 9500), ("bf16", 2, 1, 128, 12000), ("bf16", 4, 8, 128, 70),
+                                             ("bf16", 5, 8, 128, 70), ("bf16", 12, 8, 128, 60),
+                                             ("f32", 4, 8, 128, 50), ("f32", 17, 1, 64, 90)])
 def test_compact_rows(dtype, L, Hkv, D, N):
     import torch
     dev = torch.device("cuda")
