@@ -118,6 +118,9 @@ int64_t total_positions(const ikv_session *sess, int B) {
   return total;
 }
 
+// score_sizes() leaves whole products of these unrounded: every block stays 256-byte aligned.
+static_assert(ikv::HC % 64 == 0 && ikv::HIDDEN % 64 == 0 && ikv::KVF_BF16 % 128 == 0, "blocks of 64 floats");
+
 size_t score_bytes(const ikv_pool *p, const ikv_session *s, int B, uint32_t flags) {
   const bool resid = (flags & IKV_RESIDUAL) != 0;
   const int units = p->L * p->Hkv;
